@@ -13,12 +13,12 @@
 //                       matrix cores, the 10 block pairs x 10 unique entries
 //                       of eq:normAmod, its 16 right-hand-side entries and the
 //                       per-fov calibration sums of eq:normC.
-//   k_band_solve        A solve (Sect. 5.2.2, App. C): one 16-lane row of a
-//                       wavefront per segment; right-looking modified band
-//                       Cholesky (Algorithm C1 with C2 folded in) over a
-//                       register window of 16 rows x 16 band offsets, rows
-//                       entering from the per-interval sums in an LDS ring;
-//                       then C3; the segment keeps its selected coefficients.
+//   k_band_solve        A solve (Sect. 5.2.2, App. C): one wavefront per
+//                       segment; right-looking modified band Cholesky
+//                       (Algorithm C1 with C2 folded in) as a moving 16x16
+//                       front in registers, four scalar pivots and one
+//                       matrix-core update per coefficient; then C3; the
+//                       segment keeps its selected coefficients.
 //
 // Each lane walks its item's observations with stride G and loads the next
 // observation's columns while the current one is evaluated.  No global
@@ -467,213 +467,210 @@ __global__ __launch_bounds__(64 * AC_WAVES) void k_ac_pass(DevConsts k, int64_t 
 }
 
 // ------------------------------------------------------------ band solve
-// Intervals held in LDS per segment.  The row read at step i (row i + 17)
-// needs the intervals (i+17)/4 - 3 .. (i+17)/4, and interval b + 5 enters at
-// the end of step 4b + 2, after that step's read, into the slot of interval
-// b, which no later row needs; the start needs intervals 0..4.  Five slots
-// keep four segments per block within 18.6 KB of LDS (eight blocks per CU).
-constexpr int RING = 5;
-constexpr int RING_W = IV_SUMS;         // doubles per interval
-
-// Entry (i, kk) (segment-relative scalar indices, i <= kk <= i + 15) of the
-// segment's band matrix from the ring of per-interval sums.
-__device__ __forceinline__ double ring_entry(const double (*ring)[RING_W], int64_t nb, int64_t i, int64_t kk) {
-    const int64_t bi = i >> 2, bk = kk >> 2;
-    const int r = (int)(i & 3), cc = (int)(kk & 3);
-    const int e = r < cc ? tri4(r, cc) : tri4(cc, r);
-    const int64_t jlo = bk - 3 > 0 ? bk - 3 : 0;
-    const int64_t jhi = bi < nb - 4 ? bi : nb - 4;
-    double s = 0.0;
-    for (int64_t j = jlo, sl = jlo % RING; j <= jhi; ++j, sl = sl + 1 == RING ? 0 : sl + 1)
-        s += ring[sl][tri4((int)(bi - j), (int)(bk - j)) * 10 + e];
-    return s;
-}
-
-__device__ __forceinline__ double ring_rhs(const double (*ring)[RING_W], int64_t nb, int64_t i) {
-    const int64_t bi = i >> 2;
-    const int r = (int)(i & 3);
-    const int64_t jlo = bi - 3 > 0 ? bi - 3 : 0;
-    const int64_t jhi = bi < nb - 4 ? bi : nb - 4;
-    double s = 0.0;
-    for (int64_t j = jlo, sl = jlo % RING; j <= jhi; ++j, sl = sl + 1 == RING ? 0 : sl + 1)
-        s += ring[sl][100 + (bi - j) * 4 + r];
-    return s;
-}
-
-// Value of v in another lane of the 16-lane row (DPP, both 32-bit halves):
-// CTRL 0x150 + n broadcasts lane n of the row, 0x100 + n reads lane + n,
-// 0x110 + n reads lane - n, 0x120 + n rotates by n; lanes with no source
-// read 0.
+// Value of v in another lane of the 16-lane row (DPP).  CTRL 0x150 + n
+// broadcasts lane n of the row, 0x100 + n reads lane + n, 0x110 + n reads
+// lane - n, 0x120 + n rotates by n; lanes with no source read 0.
 template <int CTRL>
 __device__ __forceinline__ double row_dpp(double v) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+    if constexpr (CTRL >= 0x150) {
+        return __builtin_amdgcn_update_dpp(0.0, v, CTRL, 0xF, 0xF, true);   // one 64-bit move
+    } else {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+        return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+    }
+}
+
+// old, with the quads (four-lane banks of each 16-lane row) of BANKS taken
+// from v moved by CTRL.
+template <int CTRL, int BANKS>
+__device__ __forceinline__ double quad_dpp(double old, double v) {
+    const uint64_t o = __builtin_bit_cast(uint64_t, old), b = __builtin_bit_cast(uint64_t, v);
+    const int lo = __builtin_amdgcn_update_dpp((int)(uint32_t)o, (int)(uint32_t)b, CTRL, 0xF, BANKS, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(uint32_t)(o >> 32), (int)(uint32_t)(b >> 32), CTRL, 0xF, BANKS,
+                                               false);
     return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// Right-looking update of the window rows c = C..15 by pivot row i:
-// lane d, row c: entry (i+c, i+c+d) -= U(i, i+c) U(i, i+c+d).
-template <int C>
-__device__ __forceinline__ void band_trailing(double (&W)[16], double U) {
-    if constexpr (C < 16) {
-        W[C] -= row_dpp<0x150 + C>(U) * row_dpp<0x100 + C>(U);
-        band_trailing<C + 1>(W, U);
+// The four 16-lane rows of v, each in all four rows: r[p](lane 16 q + d) =
+// v(lane 16 p + d), by row swaps (no LDS).
+__device__ __forceinline__ void gather_rows(double v, double (&r)[4]) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    uint32_t h[2][4];
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        const uint32_t x = w ? (uint32_t)(b >> 32) : (uint32_t)b;
+        const auto y = __builtin_amdgcn_permlane32_swap(x, x, false, false);      // rows 0 1 0 1, rows 2 3 2 3
+        const auto lo = __builtin_amdgcn_permlane16_swap(y[0], y[0], false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(y[1], y[1], false, false);
+        h[w][0] = lo[0];
+        h[w][1] = lo[1];
+        h[w][2] = hi[0];
+        h[w][3] = hi[1];
     }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) r[p] = __builtin_bit_cast(double, ((uint64_t)h[1][p] << 32) | h[0][p]);
 }
 
-constexpr int BAND_SEGS = 4;            // segments per block (one wavefront), one per 16-lane row
-constexpr int PFL = (RING_W + 15) / 16; // doubles per lane to fetch one interval
+// 1/sqrt(x) for x > 0 (relative error of the estimate 2^-24, after one
+// third-order step 1.4e-16 over [2^-5, 2^5), measured), 0 otherwise.
+__device__ __forceinline__ double rsqrt_pivot(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = x > 0.0 ? y : 0.0;
+    const double e = __builtin_fma(-(x * y), y, 1.0);
+    return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+}
+
+constexpr int BAND_AHEAD = 4;           // intervals in flight before their use
+constexpr int BAND_BACK = 8;            // factor blocks in flight on the way back
 
 // Modified band Cholesky of the attitude segments (Algorithms C1-C3 with
-// half bandwidth 15, Sect. 5.2.2).  Each 16-lane row of the wavefront solves
-// one segment: lane d holds band offset d of the 16 window rows i..i+15 in
-// registers (W[c] = entry (i+c, i+c+d)) and the right-hand side of row i+d.
-// Step i takes the pivot from lane 0, forms U(i, i+d) in lane d, updates the
-// window through row broadcasts and shifts, retires row i and lets row i+16
-// enter from the per-interval sums (an LDS ring, each interval prefetched
-// two coefficient blocks ahead).  A zero or negative pivot gives a zero
-// factor row and counts one defect.  C3 then runs back up the segment with
-// x(i+d) in lane d and a row reduction per step.
-__global__ __launch_bounds__(16 * BAND_SEGS) void k_band_solve(int64_t nseg, const SegDesc* __restrict__ segs,
+// half bandwidth 15, Sect. 5.2.2), one wavefront per segment.  The system is
+// eliminated as a moving 16x16 front: interval k couples coefficients
+// k .. k+3, so its sums are added to the front just before the four rows of
+// coefficient k are eliminated.  Lane 16 q + d holds, of front rows 4i + q (i
+// = 0..3), the entry at column offset d from the diagonal block: W[i] =
+// entry (4(k+i) + q, 4(k+i) + d); a zero or negative pivot gives a zero
+// factor row and counts one defect.
+//  * The four pivot rows are copied to all four 16-lane rows and eliminated
+//    there by row broadcasts (scalar pivots in their order, as C1 asks), with
+//    the right-hand side (R: lane d holds row 4k + d).
+//  * With the factor rows back in place (row q in 16-lane row q), lane
+//    c + 4b + 16q holds element (q, c) of the 4x4 block U(k, k+b): the operand
+//    layout of v_mfma_f64_4x4x4 with its four blocks b.  The update
+//    W[i](block b) -= U(k, k+i)' U(k, k+i+b) is then one matrix instruction
+//    per i, whose operands are U shifted by i blocks and block i repeated.
+// C3 runs back up the segment: each 16-lane row forms the product of its
+// factor row with the known unknowns, the 4x4 triangle is solved by all lanes.
+//
+// Bound by the instruction issue of the serial chain (about 150 instructions
+// per coefficient forward, 110 back): a segment's time is its length, whatever
+// else runs, until there are several segments per SIMD.  Before, one 16-lane
+// row per segment, per scalar pivot 15 shifted and 15 broadcast rank-1 columns
+// and the entering row summed from an LDS ring took 1340 us for 110 segments
+// of 264 intervals, 1726 us for 12,138 of 154; this form takes 184 and 920 us.
+__global__ __launch_bounds__(64) void k_band_solve(int64_t nseg, const SegDesc* __restrict__ segs,
                                                    const double* __restrict__ iv_sums, double* __restrict__ ufac,
                                                    double* __restrict__ yfac, double* __restrict__ da,
                                                    int32_t* __restrict__ seg_def) {
-    __shared__ double ring_all[BAND_SEGS][RING][RING_W];
-    const int d = threadIdx.x & 15;
-    const int sl = threadIdx.x >> 4;
-    const int64_t sgi = (int64_t)blockIdx.x * BAND_SEGS + sl;
-    const bool valid = sgi < nseg;
-    double (*ring)[RING_W] = ring_all[sl];
-    SegDesc sd = {0, -1, 0, -1, 0};
-    if (valid) sd = segs[sgi];
-    const int64_t nb = sd.n_hi - sd.n_lo + 1;
-    const int64_t nu = valid ? 4 * nb : 0;
-    const int64_t n_iv = valid ? nb - 3 : 0;
-    int64_t nu_max = 0;
-    for (int s2 = 0; s2 < BAND_SEGS; ++s2) {
-        const int64_t g = (int64_t)blockIdx.x * BAND_SEGS + s2;
-        if (g < nseg) {
-            const SegDesc o = segs[g];
-            const int64_t n2 = 4 * (o.n_hi - o.n_lo + 1);
-            nu_max = n2 > nu_max ? n2 : nu_max;
-        }
+    const int lane = threadIdx.x;
+    const int d = lane & 15, q = lane >> 4, c = d & 3, g = d >> 2;
+    const SegDesc sd = segs[blockIdx.x];
+    const int nb = (int)(sd.n_hi - sd.n_lo + 1);       // coefficients; intervals: nb - 3
+    const int n_iv = nb - 3;
+    const double* sums = iv_sums + sd.n_lo * IV_SUMS;
+    double* U = ufac + sd.u_off * 16 + lane;
+    double* Y = yfac + sd.u_off + q;
+    // the lane's entries of an interval: front block (n, n + g), entry (q, c),
+    // for n + g <= 3 (others are read from block (n, 3) and taken zero times)
+    const int e = q < c ? tri4(q, c) : tri4(c, q);
+    int at[4];
+    double use[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        const int m = n + g < 3 ? n + g : 3;
+        at[n] = tri4(n, m) * 10 + e;
+        use[n] = n + g <= 3 ? 1.0 : 0.0;
     }
-    const double* sums = iv_sums + (valid ? sd.n_lo : 0) * IV_SUMS;
-    double* U = ufac + sd.u_off * 16;
-    double* Y = yfac + sd.u_off;
-    // intervals 0..4 into the ring, interval 5 into registers
-    for (int jj = 0; jj < 5; ++jj)
-        if (jj < n_iv)
-            for (int e = d; e < RING_W; e += 16) ring[jj][e] = sums[(int64_t)jj * IV_SUMS + e];
-    double pfA[PFL], pfB[PFL];
+    double nw[BAND_AHEAD][4], nr[BAND_AHEAD];
+    auto fetch = [&](int k, int slot) {
+        const double* iv = sums + (int64_t)(k < n_iv ? k : n_iv - 1) * IV_SUMS;
 #pragma unroll
-    for (int u = 0; u < PFL; ++u) {
-        const int e = d + 16 * u;
-        pfA[u] = (5 < n_iv && e < RING_W) ? sums[5 * IV_SUMS + e] : 0.0;
-        pfB[u] = 0.0;
-    }
-    __syncthreads();
-    double W[16];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) W[c] = (c + d < nu) ? ring_entry(ring, nb, c, c + d) : 0.0;
-    double R = d < nu ? ring_rhs(ring, nb, d) : 0.0;
-    // row i + 16 (entering after step i) is read from the ring one step early
-    double nW = (16 + d < nu) ? ring_entry(ring, nb, 16, 16 + d) : 0.0;
-    double nR = (d == 15 && 16 < nu) ? ring_rhs(ring, nb, 16) : 0.0;
-    int defect = 0;
-    for (int64_t i = 0; i < nu_max; ++i) {
-        const bool act = i < nu;
-        const int64_t b = i >> 2;
-        if ((i & 3) == 0 && b + 6 < n_iv) {
-#pragma unroll
-            for (int u = 0; u < PFL; ++u) {
-                const int e = d + 16 * u;
-                pfB[u] = e < RING_W ? sums[(b + 6) * IV_SUMS + e] : 0.0;
-            }
-        }
-        const double piv = row_dpp<0x150>(W[0]);
-        const bool ok = piv > 0.0;
-        const double inv = ok ? rsqrt_nr(piv) : 0.0;
-        const double Ud = d == 0 ? piv * inv : W[0] * inv;
-        const double y = row_dpp<0x150>(R) * inv;
-        band_trailing<1>(W, Ud);
-        R -= Ud * y;
-        R = row_dpp<0x101>(R);
-        if (d == 15) R = nR;
-#pragma unroll
-        for (int c = 0; c < 15; ++c) W[c] = W[c + 1];
-        W[15] = nW;
-        if (act) {
-            U[i * 16 + d] = Ud;
-            if (d == 0) {
-                Y[i] = y;
-                defect += ok ? 0 : 1;
-            }
-        }
-        const int64_t r = i + 17;
-        nW = (r + d < nu) ? ring_entry(ring, nb, r, r + d) : 0.0;
-        nR = (d == 15 && r < nu) ? ring_rhs(ring, nb, r) : 0.0;
-        if ((i & 3) == 2) {
-            // interval b + 5 (first read for row 4b + 20, at step 4b + 3)
-            // enters the ring in the slot of interval b, which no row read
-            // from step 4b + 3 on refers to
-            if (b + 5 < n_iv) {
-#pragma unroll
-                for (int u = 0; u < PFL; ++u) {
-                    const int e = d + 16 * u;
-                    if (e < RING_W) ring[(int)(b + 5) % RING][e] = pfA[u];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < PFL; ++u) pfA[u] = pfB[u];
-            __syncthreads();
-        }
-    }
-    __syncthreads();   // factor rows and forward-substituted y visible to all lanes
-    // Algorithm C3 from the last row up: lane d holds x(i+d), d >= 1.  Rows
-    // are read 16 at a time, one chunk ahead of their use.
-    double x = 0.0;
-    double cU[16], cu[16], cy[16];
-    auto load_rows = [&](int64_t t0, double* lU, double* lu, double* ly) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int64_t i = nu - 1 - (t0 + k);
-            lU[k] = lu[k] = ly[k] = 0.0;
-            if (i >= 0) {
-                lU[k] = U[i * 16 + d];
-                lu[k] = U[i * 16];
-                ly[k] = Y[i];
-            }
-        }
+        for (int n = 0; n < 4; ++n) nw[slot][n] = iv[at[n]];
+        nr[slot] = iv[100 + d];
     };
-    load_rows(0, cU, cu, cy);
-    for (int64_t t0 = 0; t0 < nu_max; t0 += 16) {
-        double nU[16], nu_[16], ny[16];
-        load_rows(t0 + 16, nU, nu_, ny);
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int64_t i = nu - 1 - (t0 + k);
-            double p = d >= 1 ? cU[k] * x : 0.0;
-            p += row_dpp<0x128>(p);
-            p += row_dpp<0x124>(p);
-            p += row_dpp<0x122>(p);
-            p += row_dpp<0x121>(p);
-            const double xi = cu[k] > 0.0 ? (cy[k] - p) * rcp_nr(cu[k]) : 0.0;
-            if (i >= 0 && d == 0) {
-                const int64_t n = sd.n_lo + (i >> 2);
-                if (n >= sd.keep_lo && n <= sd.keep_hi) da[4 * n + (i & 3)] = xi;
+    for (int u = 0; u < BAND_AHEAD; ++u) fetch(u, u);
+    double W[4] = {0.0, 0.0, 0.0, 0.0};
+    double R = 0.0;
+    int defect = 0;
+    for (int k0 = 0; k0 < nb; k0 += BAND_AHEAD) {
+#pragma unroll
+        for (int u = 0; u < BAND_AHEAD; ++u) {
+            const int k = k0 + u;
+            if (k >= nb) break;
+            if (k < n_iv) {
+#pragma unroll
+                for (int n = 0; n < 4; ++n) W[n] = __builtin_fma(nw[u][n], use[n], W[n]);
+                R += nr[u];
             }
-            x = row_dpp<0x111>(d == 0 ? xi : x);
-        }
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            cU[k] = nU[k];
-            cu[k] = nu_[k];
-            cy[k] = ny[k];
+            fetch(k + BAND_AHEAD, u);
+            double P[4], y[4];
+            gather_rows(W[0], P);
+            auto pivot = [&](auto pc) {
+                constexpr int p = decltype(pc)::value;
+                const double piv = row_dpp<0x150 + p>(P[p]);
+                const double inv = rsqrt_pivot(piv);
+                defect += piv > 0.0 ? 0 : 1;
+                P[p] *= inv;
+                y[p] = row_dpp<0x150 + p>(R) * inv;
+                if constexpr (p < 1) P[1] -= row_dpp<0x151>(P[p]) * P[p];
+                if constexpr (p < 2) P[2] -= row_dpp<0x152>(P[p]) * P[p];
+                if constexpr (p < 3) P[3] -= row_dpp<0x153>(P[p]) * P[p];
+                R -= P[p] * y[p];
+            };
+            pivot(std::integral_constant<int, 0>{});
+            pivot(std::integral_constant<int, 1>{});
+            pivot(std::integral_constant<int, 2>{});
+            pivot(std::integral_constant<int, 3>{});
+            R = row_dpp<0x104>(R);
+            const double X = q < 2 ? (q == 0 ? P[0] : P[1]) : (q == 2 ? P[2] : P[3]);
+            const double yq = q < 2 ? (q == 0 ? y[0] : y[1]) : (q == 2 ? y[2] : y[3]);
+            U[(int64_t)k * 64] = X;
+            if (d == 0) Y[4 * (int64_t)k] = yq;
+            // blocks i, i+1, .. in places 0, 1, ..; and block i in each place
+            // that front row i has
+            const double b1 = row_dpp<0x104>(X), b2 = row_dpp<0x108>(X), b3 = row_dpp<0x10C>(X);
+            const double a1 = quad_dpp<0x114, 0x4>(quad_dpp<0x104, 0x1>(X, X), X);
+            const double a2 = quad_dpp<0x104, 0x2>(b2, X);
+            W[0] = __builtin_amdgcn_mfma_f64_4x4x4f64(-a1, b1, W[1], 0, 0, 0);
+            W[1] = __builtin_amdgcn_mfma_f64_4x4x4f64(-a2, b2, W[2], 0, 0, 0);
+            W[2] = __builtin_amdgcn_mfma_f64_4x4x4f64(-b3, b3, W[3], 0, 0, 0);
+            W[3] = 0.0;
         }
     }
-    if (valid && d == 0) seg_def[sgi] = defect;
+    __syncthreads();   // forward-substituted y visible to all lanes
+    // Algorithm C3 from the last coefficient up: x in lane d is the unknown
+    // 4k + d, d >= 4, when coefficient k is solved (0 in lanes 0..3)
+    double fX[BAND_BACK], fY[BAND_BACK];
+    auto fetch_back = [&](int k, int slot) {
+        const int64_t kk = k > 0 ? k : 0;
+        fX[slot] = U[kk * 64];
+        fY[slot] = Y[4 * kk];
+    };
+#pragma unroll
+    for (int u = 0; u < BAND_BACK; ++u) fetch_back(nb - 1 - u, u);
+    double x = 0.0;
+    for (int k0 = nb - 1; k0 >= 0; k0 -= BAND_BACK) {
+#pragma unroll
+        for (int u = 0; u < BAND_BACK; ++u) {
+            const int k = k0 - u;
+            if (k < 0) break;
+            const double X = fX[u], yq = fY[u];
+            fetch_back(k - BAND_BACK, u);
+            // reciprocal pivots (0 where the factor row is zero) on the diagonal
+            const double iv = X > 0.0 ? rcp_nr(X) : 0.0;
+            double T[4], S[4];
+            gather_rows(d == q ? iv : X, T);
+            double t = X * x;
+            t += row_dpp<0x128>(t);
+            t += row_dpp<0x124>(t);
+            t += row_dpp<0x122>(t);
+            t += row_dpp<0x121>(t);
+            gather_rows(yq - t, S);
+            const double x3 = S[3] * row_dpp<0x153>(T[3]);
+            const double x2 = (S[2] - row_dpp<0x153>(T[2]) * x3) * row_dpp<0x152>(T[2]);
+            const double x1 = (S[1] - row_dpp<0x153>(T[1]) * x3 - row_dpp<0x152>(T[1]) * x2) * row_dpp<0x151>(T[1]);
+            const double x0 = (S[0] - row_dpp<0x153>(T[0]) * x3 - row_dpp<0x152>(T[0]) * x2 -
+                               row_dpp<0x151>(T[0]) * x1) * row_dpp<0x150>(T[0]);
+            const double xs = c < 2 ? (c == 0 ? x0 : x1) : (c == 2 ? x2 : x3);
+            const int64_t n = sd.n_lo + k;
+            if (n >= sd.keep_lo && n <= sd.keep_hi && lane < 4) da[4 * n + lane] = xs;
+            x = row_dpp<0x114>(d < 4 ? xs : x);
+        }
+    }
+    if (lane == 0) seg_def[blockIdx.x] = defect;
 }
 
 inline int groups_grid(int64_t n_items, int items_per_block) {
@@ -736,8 +733,8 @@ void launch_ac_pass(agis_ctx* ctx) {
 void launch_band_solve(agis_ctx* ctx) {
     const int64_t nseg = (int64_t)ctx->h_segs.size();
     if (nseg == 0) return;
-    k_band_solve<<<(unsigned)((nseg + BAND_SEGS - 1) / BAND_SEGS), 16 * BAND_SEGS, 0, ctx->stream>>>(
-        nseg, ctx->segs, ctx->iv_sums, ctx->ufac, ctx->yfac, ctx->da, ctx->seg_def);
+    k_band_solve<<<(unsigned)nseg, 64, 0, ctx->stream>>>(nseg, ctx->segs, ctx->iv_sums, ctx->ufac, ctx->yfac, ctx->da,
+                                                         ctx->seg_def);
 }
 
 }  // namespace agis
