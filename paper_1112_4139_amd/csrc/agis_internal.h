@@ -36,6 +36,20 @@ struct SClass {
     int cap, nt;
 };
 
+// Arrays whose statistics a call returns: x [n][w] (w <= 5; rms and maximum
+// per column), the sums of extra [n] and of iextra [n_i] (either may be null).
+struct StatJob {
+    const double* x;
+    int64_t n;
+    int w;
+    const double* extra;
+    const int32_t* iextra;
+    int64_t n_i;
+};
+struct StatJobs {
+    StatJob job[3];
+};
+
 struct Timers {
     hipEvent_t ev[10][2];
     bool valid[10];
@@ -144,7 +158,9 @@ struct agis_ctx {
     double* red = nullptr;               // reduction scratch
     int64_t red_len = 0;
     double* eo = nullptr;                // [8] frame rotator parameters on device
-    double* stat = nullptr;              // statistics scratch
+    double* stat = nullptr;              // results read by the host after a call: pinned host memory [64]
+                                         // that kernels write ([0, 36) statistics, [36, 42) frame parameters,
+                                         // [48, 50) scalars of the iteration schemes)
 
     // robust mode: excess attitude noise per bucket, per-source varsigma,
     // and the seven by-source columns of the inner iteration (the first one
@@ -213,7 +229,6 @@ struct agis_ctx {
     double* cg_sy = nullptr;             // sources of the point being evaluated
     double* cg_part = nullptr;           // reduction partials [CG_BLOCKS][2] and of p'N p
     double* cg_qpart = nullptr;
-    double* cg_out = nullptr;            // results [2]
     int cg_k = 0;                        // iterations done in the current cycle (0: a cycle starts)
     double cg_rho = 0.0;                 // r'z
     uint64_t cg_ver = 0;                 // state version the CG vectors belong to
@@ -294,16 +309,14 @@ int load_geometry(agis_ctx* ctx, const int8_t* ccd, const float* mu, int32_t n_c
 void launch_geo_eta(agis_ctx* ctx);
 void launch_geo_solve(agis_ctx* ctx);
 void launch_geo_basic_angle(agis_ctx* ctx, double* out);   // out: device [n_cells / 2]
-void launch_apply_attitude(agis_ctx* ctx);
 void launch_global_solve(agis_ctx* ctx);
-void launch_apply_add(agis_ctx* ctx, int64_t n, double* x, const double* dx);   // x += dx
-void launch_apply_calibration(agis_ctx* ctx);
+// x += dx and y += dy in one launch
+void launch_apply_add(agis_ctx* ctx, int64_t n, double* x, const double* dx, int64_t m = 0, double* y = nullptr,
+                      const double* dy = nullptr);
 void launch_frame_fit(agis_ctx* ctx);
 void launch_frame_apply(agis_ctx* ctx);
 void launch_residuals(agis_ctx* ctx, double* R_input_order);
-// statistics over n rows of width w (rms and max per column, col < 5);
-// out[0..4] = rms, out[5..9] = max, out[10] = scalar sum of extra (or 0)
-void launch_stats(agis_ctx* ctx, const double* x, int64_t n, int w, const double* extra, const int32_t* iextra,
-                  double* out);
+// statistics of each job; out [job][12]: rms[5], max[5], sum of extra, sum of iextra
+void launch_stats(agis_ctx* ctx, const StatJobs& jobs, int n_jobs, double* out);
 
 }  // namespace agis

@@ -170,7 +170,7 @@ static void free_store(agis_ctx* ctx) {
     dfree(ctx->chi2_part);
     dfree(ctx->chi2_out);
     for (double** v : {&ctx->cg_r, &ctx->cg_z, &ctx->cg_p, &ctx->cg_ry, &ctx->cg_zy, &ctx->cg_sy, &ctx->cg_part,
-                       &ctx->cg_qpart, &ctx->cg_out})
+                       &ctx->cg_qpart})
         dfree(*v);
     ctx->cg_k = 0;
     ctx->lh_count = 0;
@@ -402,7 +402,10 @@ extern "C" int agis_create(const agis_config_t* cfg, agis_ctx_t** out) {
     ctx->red_len = 1 << 16;
     if ((rc = dalloc(ctx, &ctx->red, ctx->red_len, "reduction scratch")) != AGIS_OK) return fail(rc);
     if ((rc = dalloc(ctx, &ctx->eo, 8, "frame parameters")) != AGIS_OK) return fail(rc);
-    if ((rc = dalloc(ctx, &ctx->stat, 64, "statistics")) != AGIS_OK) return fail(rc);
+    if (hipHostMalloc((void**)&ctx->stat, 64 * sizeof(double), hipHostMallocCoherent) != hipSuccess) {
+        ctx->stat = nullptr;
+        return fail(set_error(ctx, AGIS_E_OOM, "host allocation failed: results"));
+    }
     for (int w = 0; w < 2; ++w) {
         const int nw = mlp_num_weights(w);
         if ((rc = dalloc(ctx, &ctx->mlp_w[w], nw, "mlp weights")) != AGIS_OK) return fail(rc);
@@ -469,7 +472,7 @@ extern "C" void agis_destroy(agis_ctx_t* ctx) {
     dfree(ctx->yfac);
     dfree(ctx->red);
     dfree(ctx->eo);
-    dfree(ctx->stat);
+    if (ctx->stat) (void)hipHostFree(ctx->stat);
     dfree(ctx->eps_a2);
     for (int w = 0; w < 2; ++w) {
         dfree(ctx->mlp_w[w]);
@@ -711,26 +714,6 @@ static double tget(agis_ctx* ctx, int e) {
     return (double)ms;
 }
 
-static int fill_stats(agis_ctx* ctx, agis_block_stats_t* st, const double* x, int64_t n, int w,
-                      const double* extra, const int32_t* iextra, int64_t n_obs, int64_t n_units) {
-    if (!st) return AGIS_OK;
-    launch_stats(ctx, x, n, w, extra, iextra, ctx->stat);
-    HIPCHK(hipGetLastError());
-    double h[12];
-    HIPCHK(hipMemcpyAsync(h, ctx->stat, sizeof h, hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(hipStreamSynchronize(ctx->stream));
-    std::memset(st, 0, sizeof(*st));
-    for (int e = 0; e < 5; ++e) {
-        st->rms_update[e] = h[e];
-        st->max_update[e] = h[5 + e];
-    }
-    st->chi2 = h[10];
-    st->defect = (int64_t)std::llround(h[11]);
-    st->n_obs = n_obs;
-    st->n_units = n_units;
-    return AGIS_OK;
-}
-
 static int run_source(agis_ctx* ctx) {
     tstart(ctx, T_S);
     if (robust_now(ctx)) launch_source_update_robust(ctx);
@@ -774,45 +757,60 @@ static int run_ac(agis_ctx* ctx, bool do_a, bool do_c, bool eps_update = false, 
         launch_global_solve(ctx);
         HIPCHK(hipGetLastError());
     }
-    if (do_a && apply) launch_apply_attitude(ctx);
-    if (do_c && apply) {
-        if (ctx->geo_ccds > 0) {
-            launch_apply_add(ctx, 3 * ctx->n_groups + ctx->n_small, ctx->geo, ctx->dgeo);
-            launch_geo_eta(ctx);
-        } else {
-            launch_apply_calibration(ctx);
-        }
+    // one launch for the attitude's and the calibration's updates
+    const int64_t n_a = do_a && apply ? 4 * ctx->N : 0;
+    if (do_c && apply && ctx->geo_ccds > 0) {
+        launch_apply_add(ctx, n_a, ctx->a, ctx->da, 3 * ctx->n_groups + ctx->n_small, ctx->geo, ctx->dgeo);
+        launch_geo_eta(ctx);
+    } else {
+        launch_apply_add(ctx, n_a, ctx->a, ctx->da, do_c && apply ? ctx->n_cells : 0, ctx->c, ctx->dc);
     }
     if (do_g && apply) launch_apply_add(ctx, 1, ctx->gpar, ctx->dgpar);
     HIPCHK(hipGetLastError());
     return AGIS_OK;
 }
 
-static int stats_s(agis_ctx* ctx, agis_block_stats_t* st) {
-    if (!st) return AGIS_OK;
-    int rc = fill_stats(ctx, st, ctx->ds, ctx->n_src, 5, ctx->qsrc, ctx->sdef, ctx->n_obs, ctx->n_src);
-    if (rc == AGIS_OK) st->ms = tget(ctx, T_S);
-    return rc;
-}
-static int stats_a(agis_ctx* ctx, agis_block_stats_t* st) {
-    if (!st) return AGIS_OK;
-    int rc = fill_stats(ctx, st, ctx->da, ctx->N, 4, nullptr, nullptr, ctx->n_obs, ctx->N);
-    if (rc) return rc;
-    // summed rank-defect count over the segments
-    agis_block_stats_t tmp;
-    rc = fill_stats(ctx, &tmp, nullptr, (int64_t)ctx->h_segs.size(), 0, nullptr, ctx->seg_def, 0, 0);
-    if (rc) return rc;
-    st->defect = tmp.defect;
-    st->ms = tget(ctx, T_AC) + tget(ctx, T_BAND);
+// Statistics of the blocks asked for (any may be null), all in one launch
+// and one wait.  The update arrays of a block stay as it left them until its
+// next run, so an iteration reads all three at its end.
+static int read_stats(agis_ctx* ctx, agis_block_stats_t* s, agis_block_stats_t* a, agis_block_stats_t* c) {
+    StatJobs jobs = {};
+    agis_block_stats_t* to[3];
+    int n = 0;
+    if (s) {
+        jobs.job[n] = {ctx->ds, ctx->n_src, 5, ctx->qsrc, ctx->sdef, ctx->n_src};
+        to[n++] = s;
+    }
+    if (a) {
+        // the summed rank-defect count over the segments
+        jobs.job[n] = {ctx->da, ctx->N, 4, nullptr, ctx->seg_def, (int64_t)ctx->h_segs.size()};
+        to[n++] = a;
+    }
+    if (c) {
+        if (ctx->geo_ccds > 0) jobs.job[n] = {ctx->dgeo, ctx->n_groups, 3, nullptr, nullptr, 0};
+        else jobs.job[n] = {ctx->dc, ctx->n_cells, 1, nullptr, nullptr, 0};
+        to[n++] = c;
+    }
+    if (n == 0) return AGIS_OK;
+    launch_stats(ctx, jobs, n, ctx->stat);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    for (int j = 0; j < n; ++j) {
+        const double* h = ctx->stat + 12 * j;
+        std::memset(to[j], 0, sizeof(*to[j]));
+        for (int e = 0; e < 5; ++e) {
+            to[j]->rms_update[e] = h[e];
+            to[j]->max_update[e] = h[5 + e];
+        }
+        to[j]->chi2 = h[10];
+        to[j]->defect = (int64_t)std::llround(h[11]);
+        to[j]->n_obs = ctx->n_obs;
+        to[j]->n_units = jobs.job[j].n;
+    }
+    if (s) s->ms = tget(ctx, T_S);
+    if (a) a->ms = tget(ctx, T_AC) + tget(ctx, T_BAND);
+    if (c) c->ms = tget(ctx, T_CAL);
     return AGIS_OK;
-}
-static int stats_c(agis_ctx* ctx, agis_block_stats_t* st) {
-    if (!st) return AGIS_OK;
-    int rc = ctx->geo_ccds > 0
-                 ? fill_stats(ctx, st, ctx->dgeo, ctx->n_groups, 3, nullptr, nullptr, ctx->n_obs, ctx->n_groups)
-                 : fill_stats(ctx, st, ctx->dc, ctx->n_cells, 1, nullptr, nullptr, ctx->n_obs, ctx->n_cells);
-    if (rc == AGIS_OK) st->ms = tget(ctx, T_CAL);
-    return rc;
 }
 
 extern "C" int agis_source_update(agis_ctx_t* ctx, agis_block_stats_t* st) {
@@ -821,8 +819,7 @@ extern "C" int agis_source_update(agis_ctx_t* ctx, agis_block_stats_t* st) {
     REQUIRE_LOADED();
     int rc = run_source(ctx);
     if (rc) return rc;
-    rc = stats_s(ctx, st);
-    if (rc) return rc;
+    if (st) return read_stats(ctx, st, nullptr, nullptr);
     HIPCHK(hipStreamSynchronize(ctx->stream));
     return AGIS_OK;
 }
@@ -833,8 +830,7 @@ extern "C" int agis_attitude_update(agis_ctx_t* ctx, agis_block_stats_t* st) {
     REQUIRE_LOADED();
     int rc = run_ac(ctx, true, false);
     if (rc) return rc;
-    rc = stats_a(ctx, st);
-    if (rc) return rc;
+    if (st) return read_stats(ctx, nullptr, st, nullptr);
     HIPCHK(hipStreamSynchronize(ctx->stream));
     return AGIS_OK;
 }
@@ -845,8 +841,7 @@ extern "C" int agis_calibration_update(agis_ctx_t* ctx, agis_block_stats_t* st) 
     REQUIRE_LOADED();
     int rc = run_ac(ctx, false, true);
     if (rc) return rc;
-    rc = stats_c(ctx, st);
-    if (rc) return rc;
+    if (st) return read_stats(ctx, nullptr, nullptr, st);
     HIPCHK(hipStreamSynchronize(ctx->stream));
     return AGIS_OK;
 }
@@ -890,8 +885,7 @@ extern "C" int agis_attitude_calibration_update(agis_ctx_t* ctx, agis_block_stat
     REQUIRE_LOADED();
     int rc = run_ac(ctx, true, true);
     if (rc) return rc;
-    if ((rc = stats_a(ctx, st_a))) return rc;
-    if ((rc = stats_c(ctx, st_c))) return rc;
+    if (st_a || st_c) return read_stats(ctx, nullptr, st_a, st_c);
     HIPCHK(hipStreamSynchronize(ctx->stream));
     return AGIS_OK;
 }
@@ -948,12 +942,9 @@ static int iterate_once(agis_ctx* ctx, agis_iter_stats_t* st) {
     tstart(ctx, T_ITER);
     int rc = run_source(ctx);
     if (rc) return rc;
-    if (st && (rc = stats_s(ctx, &st->s))) return rc;
     // robust: eps_a from the residuals after the source update (Sect. 5.2.5)
     rc = run_ac(ctx, true, true, true, true, nullptr, true);
     if (rc) return rc;
-    if (st && (rc = stats_a(ctx, &st->a))) return rc;
-    if (st && (rc = stats_c(ctx, &st->c))) return rc;
     if (ctx->have_ref) {
         tstart(ctx, T_FRAME);
         launch_frame_fit(ctx);
@@ -963,13 +954,9 @@ static int iterate_once(agis_ctx* ctx, agis_iter_stats_t* st) {
     }
     tstop(ctx, T_ITER);
     if (st) {
-        if (ctx->have_ref) {
-            HIPCHK(hipMemcpyAsync(st->eps_omega, ctx->eo, 6 * sizeof(double), hipMemcpyDeviceToHost,
-                                  ctx->stream));
-        } else {
-            std::memset(st->eps_omega, 0, sizeof st->eps_omega);
-        }
-        HIPCHK(hipStreamSynchronize(ctx->stream));
+        if (ctx->have_ref) launch_copy(ctx, 6, ctx->eo, ctx->stat + 36);
+        if ((rc = read_stats(ctx, &st->s, &st->a, &st->c))) return rc;
+        for (int e = 0; e < 6; ++e) st->eps_omega[e] = ctx->have_ref ? ctx->stat[36 + e] : 0.0;
         st->ms = tget(ctx, T_ITER);
     }
     return AGIS_OK;
@@ -1671,7 +1658,6 @@ static int cg_alloc(agis_ctx* ctx) {
     if (!ctx->cg_sy) ALLOC(ctx->cg_sy, 5 * std::max<int64_t>(ctx->n_src, 1), "cg state");
     if (!ctx->cg_part) ALLOC(ctx->cg_part, 2 * 1024, "cg partial sums");
     if (!ctx->cg_qpart) ALLOC(ctx->cg_qpart, std::max<int64_t>(cg_quad_blocks(ctx), 1), "cg partial sums");
-    if (!ctx->cg_out) ALLOC(ctx->cg_out, 2, "cg sums");
     return AGIS_OK;
 }
 
@@ -1696,8 +1682,9 @@ static int cg_evaluate(agis_ctx* ctx, double* r, double* z) {
 
 static int cg_read(agis_ctx* ctx, double h[2]) {
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(h, ctx->cg_out, 2 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
+    h[0] = ctx->stat[48];
+    h[1] = ctx->stat[49];
     return AGIS_OK;
 }
 
@@ -1718,13 +1705,13 @@ static int cg_step(agis_ctx* ctx, int32_t restart, agis_cg_stats_t* st) {
         }
         if ((rc = cg_evaluate(ctx, ctx->cg_r, ctx->cg_z))) return rc;
         launch_copy(ctx, n, ctx->cg_z, ctx->cg_p);
-        launch_cg_dot(ctx, ctx->cg_r, ctx->cg_z, nullptr, ctx->cg_out);
+        launch_cg_dot(ctx, ctx->cg_r, ctx->cg_z, nullptr, ctx->stat + 48);
         if ((rc = cg_read(ctx, h))) return rc;
         ctx->cg_rho = h[0];
         ctx->cg_k = 1;
         out.cycle_start = 1;
     } else {
-        launch_cg_quad(ctx, ctx->cg_p, ctx->cg_qpart, ctx->cg_out);
+        launch_cg_quad(ctx, ctx->cg_p, ctx->cg_qpart, ctx->stat + 48);
         if ((rc = cg_read(ctx, h))) return rc;
         const double pnp = h[0];
         if (!(std::isfinite(pnp) && pnp > 0.0)) {
@@ -1736,7 +1723,7 @@ static int cg_step(agis_ctx* ctx, int32_t restart, agis_cg_stats_t* st) {
             launch_cg_step_state(ctx, ctx->cg_p, alpha);
             launch_prep_sources(ctx);
             if ((rc = cg_evaluate(ctx, ctx->cg_ry, ctx->cg_zy))) return rc;
-            launch_cg_dot2(ctx, ctx->cg_ry, ctx->cg_zy, ctx->cg_z, ctx->cg_out);   // r'z, r'z_old
+            launch_cg_dot2(ctx, ctx->cg_ry, ctx->cg_zy, ctx->cg_z, ctx->stat + 48);   // r'z, r'z_old
             if ((rc = cg_read(ctx, h))) return rc;
             double beta = ctx->cg_rho != 0.0 ? (h[0] - h[1]) / ctx->cg_rho : 0.0;
             beta = std::max(beta, 0.0);

@@ -7,6 +7,8 @@
 //
 // No global atomics: every reduction has a fixed order, so results are
 // bitwise reproducible run to run.
+#include <algorithm>
+
 #include "agis_internal.h"
 
 namespace agis {
@@ -42,9 +44,13 @@ __global__ __launch_bounds__(256) void k_prep_sources(int64_t n_src, const doubl
     }
 }
 
-__global__ void k_apply_add(int64_t n, double* __restrict__ x, const double* __restrict__ dx) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        x[i] += dx[i];
+// x += dx and, in the same launch, y += dy
+__global__ void k_apply_add(int64_t n, double* __restrict__ x, const double* __restrict__ dx, int64_t m,
+                            double* __restrict__ y, const double* __restrict__ dy) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n + m; i += (int64_t)gridDim.x * blockDim.x) {
+        if (i < n) x[i] += dx[i];
+        else y[i - n] += dy[i - n];
+    }
 }
 
 // ------------------------------------------------------ calibration solve
@@ -105,96 +111,115 @@ __global__ __launch_bounds__(256) void k_calib_solve(int64_t n_cells, const int3
     }
 }
 
+// Sums of NV values over the 256 threads of a block, in a fixed order: first
+// over each wavefront (all NV exchanges of a step are independent), then over
+// the four wavefronts; thread e receives sum e (e < NV).  A tree over LDS
+// with a barrier per step took ten times as long as the data it summed.
+template <int NV, bool MAX5 = false>
+__device__ __forceinline__ double block_sums(double (&v)[NV], double (*red)[NV]) {
+    // MAX5: values 5..9 are maxima
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1)
+#pragma unroll
+        for (int e = 0; e < NV; ++e) {
+            const double o = __shfl_xor(v[e], m, 64);
+            v[e] = MAX5 && e >= 5 && e < 10 ? fmax(v[e], o) : v[e] + o;
+        }
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int e = 0; e < NV; ++e) red[threadIdx.x >> 6][e] = v[e];
+    __syncthreads();
+    const int e = threadIdx.x < NV ? threadIdx.x : 0;
+    double s = red[0][e];
+    for (int w = 1; w < 4; ++w) s = MAX5 && e >= 5 && e < 10 ? fmax(s, red[w][e]) : s + red[w][e];
+    return s;
+}
+
 // ---------------------------------------------------------- frame rotator
 constexpr int FR_BLOCKS = 512;
-constexpr int FR_VALS = 27;   // 21 upper entries of the 6x6 matrix + 6 rhs
+// Sums per block.  With rows (0, q), (0, -p), (q, tau q), (-p, -tau p) for
+// mu_a*, mu_d, alpha*, delta (eq:cond-mu3, tau the same for every source) the
+// 6x6 matrix is (E, tau E; tau E, F + tau^2 E), E = sum w_a q q' + w_d p p'
+// and F the same with the weights of the proper motions, the right-hand side
+// (u, v + tau u): 6 + 6 + 3 + 3 sums instead of 21 + 6.
+constexpr int FR_VALS = 18;
 
 // Weighted by the inverse variances of the last S update (eq:cond-mu3 rows
 // for mu_a*, mu_d, alpha*, delta); zero or non-finite variance: zero weight.
-__global__ __launch_bounds__(256) void k_frame_fit_partial(DevConsts k, int64_t n_src, const double* __restrict__ s,
+// part: [FR_VALS][blocks].  Bound by the reduction for small catalogues
+// (20,000 sources: 34 -> 9 us with the final sum below 53 -> 6 us).
+__global__ __launch_bounds__(256) void k_frame_fit_partial(int64_t n_src, const double* __restrict__ s,
                                                            const double* __restrict__ sref,
                                                            const double* __restrict__ svar,
                                                            double* __restrict__ part) {
-    __shared__ double red[256];
+    __shared__ double red[4][FR_VALS];
     double acc[FR_VALS];
 #pragma unroll
     for (int e = 0; e < FR_VALS; ++e) acc[e] = 0.0;
-    const double tau = (k.t_ep - k.t_fr) / k.year_s;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_src;
          i += (int64_t)gridDim.x * blockDim.x) {
         const double* x = s + 5 * i;
         const double* h = sref + 5 * i;
+        const double* vi = svar + 5 * i;
         double sa, ca, sd, cd, sah, cah, sdh, cdh;
         sincos(x[0], &sa, &ca);
         sincos(x[1], &sd, &cd);
         sincos(h[0], &sah, &cah);
         sincos(h[1], &sdh, &cdh);
-        const double pt[3] = {-sa, ca, 0.0};
-        const double qt[3] = {-sd * ca, -sd * sa, cd};
+        const double p[3] = {-sa, ca, 0.0};
+        const double q[3] = {-sd * ca, -sd * sa, cd};
         const double dr[3] = {cd * ca - cdh * cah, cd * sa - cdh * sah, sd - sdh};
-        double rows[4][6], rhs[4];
+        auto weight = [](double v) { return (v > 0.0 && isfinite(v)) ? 1.0 / v : 0.0; };
+        const double wa = weight(vi[0]), wd = weight(vi[1]), wma = weight(vi[3]), wmd = weight(vi[4]);
+        const double ra = wa * dot3(p, dr), rd = wd * dot3(q, dr);
+        const double rma = wma * (x[3] - h[3]), rmd = wmd * (x[4] - h[4]);
+        int e = 0;
 #pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            rows[0][m] = 0.0;
-            rows[0][3 + m] = qt[m];
-            rows[1][m] = 0.0;
-            rows[1][3 + m] = -pt[m];
-            rows[2][m] = qt[m];
-            rows[2][3 + m] = tau * qt[m];
-            rows[3][m] = -pt[m];
-            rows[3][3 + m] = -tau * pt[m];
-        }
-        rhs[0] = x[3] - h[3];
-        rhs[1] = x[4] - h[4];
-        rhs[2] = dot3(pt, dr);
-        rhs[3] = dot3(qt, dr);
-        const double* vi = svar + 5 * i;
-        const double vv[4] = {vi[3], vi[4], vi[0], vi[1]};
+        for (int r = 0; r < 3; ++r) {
 #pragma unroll
-        for (int eq = 0; eq < 4; ++eq) {
-            const double wt = (vv[eq] > 0.0 && isfinite(vv[eq])) ? 1.0 / vv[eq] : 0.0;
-            int e = 0;
-#pragma unroll
-            for (int r = 0; r < 6; ++r) {
-                const double rw = rows[eq][r] * wt;
-#pragma unroll
-                for (int cc = r; cc < 6; ++cc) acc[e++] += rw * rows[eq][cc];
+            for (int c = r; c < 3; ++c, ++e) {
+                acc[e] += wa * q[r] * q[c] + wd * p[r] * p[c];
+                acc[6 + e] += wma * q[r] * q[c] + wmd * p[r] * p[c];
             }
-#pragma unroll
-            for (int r = 0; r < 6; ++r) acc[21 + r] += rows[eq][r] * wt * rhs[eq];
+            acc[12 + r] += ra * q[r] - rd * p[r];
+            acc[15 + r] += rma * q[r] - rmd * p[r];
         }
     }
-    for (int e = 0; e < FR_VALS; ++e) {
-        red[threadIdx.x] = acc[e];
-        __syncthreads();
-        for (int st = 128; st > 0; st >>= 1) {
-            if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) part[blockIdx.x * FR_VALS + e] = red[0];
-        __syncthreads();
-    }
+    const double v = block_sums<FR_VALS>(acc, red);
+    if (threadIdx.x < FR_VALS) part[threadIdx.x * FR_BLOCKS + blockIdx.x] = v;
 }
 
-__global__ __launch_bounds__(64) void k_frame_fit_final(const double* __restrict__ part, double* __restrict__ eo) {
+// One wavefront per sum; its lanes take FR_BLOCKS / 64 partials each.
+__global__ __launch_bounds__(1024) void k_frame_fit_final(DevConsts k, const double* __restrict__ part,
+                                                          double* __restrict__ eo) {
     __shared__ double tot[FR_VALS];
-    const int lane = threadIdx.x;
-    for (int e = 0; e < FR_VALS; ++e) {
+    const int lane = threadIdx.x & 63;
+    for (int e = threadIdx.x >> 6; e < FR_VALS; e += 16) {
         double v = 0.0;
-        for (int b = lane; b < FR_BLOCKS; b += 64) v += part[b * FR_VALS + e];
+#pragma unroll
+        for (int b = 0; b < FR_BLOCKS / 64; ++b) v += part[e * FR_BLOCKS + 64 * b + lane];
         v = wave_sum(v);
         if (lane == 0) tot[e] = v;
     }
     __syncthreads();
-    if (lane == 0) {
-        double U[36], x[6];
-        int e = 0;
-        for (int r = 0; r < 6; ++r)
-            for (int cc = r; cc < 6; ++cc) U[r * 6 + cc] = tot[e++];
-        for (int r = 0; r < 6; ++r) x[r] = tot[21 + r];
-        small_chol_solve<6>(U, x);
-        for (int r = 0; r < 6; ++r) eo[r] = x[r];
+    if (threadIdx.x != 0) return;
+    const double tau = (k.t_ep - k.t_fr) / k.year_s;
+    double U[36], x[6];
+    int e = 0;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+#pragma unroll
+        for (int c = r; c < 3; ++c, ++e) {
+            U[r * 6 + c] = tot[e];
+            U[r * 6 + 3 + c] = U[c * 6 + 3 + r] = tau * tot[e];
+            U[(3 + r) * 6 + 3 + c] = tot[6 + e] + tau * tau * tot[e];
+        }
+        x[r] = tot[12 + r];
+        x[3 + r] = tot[15 + r] + tau * tot[12 + r];
     }
+    small_chol_solve<6>(U, x);
+#pragma unroll
+    for (int r = 0; r < 6; ++r) eo[r] = x[r];
 }
 
 // f(t) = Q[(t - t_fr) omega] Q(eps) (eq:fr1)
@@ -209,13 +234,13 @@ __device__ __forceinline__ void frame_quat(const DevConsts& k, const double* eo,
 
 // Rigorous transformation of the astrometric parameters (Sect. 6.1.2,
 // steps 1-5) and of the source data used by the time-ordered pass.
-__global__ __launch_bounds__(256) void k_frame_apply_sources(DevConsts k, int64_t n_src, const double* __restrict__ eo,
-                                                             double* __restrict__ s, SrcPrep* __restrict__ prep) {
+__device__ __forceinline__ void frame_apply_sources(const DevConsts& k, int64_t first, int64_t stride, int64_t n_src,
+                                                    const double* __restrict__ eo, double* __restrict__ s,
+                                                    SrcPrep* __restrict__ prep) {
     double f[4], A[9];
     frame_quat(k, eo, k.t_ep, f);
     quat2mat(f, A);
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_src;
-         i += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t i = first; i < n_src; i += stride) {
         double* x = s + 5 * i;
         double sa, ca, sd, cd;
         sincos(x[0], &sa, &ca);
@@ -256,9 +281,10 @@ __global__ __launch_bounds__(256) void k_frame_apply_sources(DevConsts k, int64_
 }
 
 // eq:fr-q4 with the support mid-time eq:RF4.
-__global__ __launch_bounds__(256) void k_frame_apply_attitude(DevConsts k, int64_t N, const double* __restrict__ eo,
-                                                              const double* __restrict__ knots, double* __restrict__ a) {
-    for (int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; n < N; n += (int64_t)gridDim.x * blockDim.x) {
+__device__ __forceinline__ void frame_apply_attitude(const DevConsts& k, int64_t first, int64_t stride, int64_t N,
+                                                     const double* __restrict__ eo, const double* __restrict__ knots,
+                                                     double* __restrict__ a) {
+    for (int64_t n = first; n < N; n += stride) {
         const double tbar = 0.5 * (knots[n] + knots[n + 4]);
         double f[4];
         frame_quat(k, eo, tbar, f);
@@ -272,6 +298,19 @@ __global__ __launch_bounds__(256) void k_frame_apply_attitude(DevConsts k, int64
         an[2] = r[2];
         an[3] = r[3];
     }
+}
+
+// Both in one launch: the first src_blocks blocks take the sources.
+__global__ __launch_bounds__(256) void k_frame_apply(DevConsts k, int src_blocks, int64_t n_src, int64_t N,
+                                                     const double* __restrict__ eo, double* __restrict__ s,
+                                                     SrcPrep* __restrict__ prep, const double* __restrict__ knots,
+                                                     double* __restrict__ a) {
+    const int64_t b = blockIdx.x;
+    if (b < src_blocks)
+        frame_apply_sources(k, b * 256 + threadIdx.x, (int64_t)src_blocks * 256, n_src, eo, s, prep);
+    else
+        frame_apply_attitude(k, (b - src_blocks) * 256 + threadIdx.x, (int64_t)(gridDim.x - src_blocks) * 256, N, eo,
+                             knots, a);
 }
 
 // ------------------------------------------------------------ residuals
@@ -301,48 +340,47 @@ __global__ __launch_bounds__(256) void k_residuals(DevConsts k, int64_t K, const
 }
 
 // ----------------------------------------------------------- statistics
-constexpr int ST_BLOCKS = 256;
-__global__ __launch_bounds__(256) void k_stats_partial(const double* __restrict__ x, int64_t n, int w,
-                                                       const double* __restrict__ extra,
-                                                       const int32_t* __restrict__ iextra, double* __restrict__ part) {
-    __shared__ double red[256];
-    double ss[5] = {0, 0, 0, 0, 0}, mx[5] = {0, 0, 0, 0, 0}, ex = 0.0, iex = 0.0;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        for (int cc = 0; cc < w && cc < 5; ++cc) {
-            const double v = x[i * w + cc];
-            ss[cc] += v * v;
-            mx[cc] = fmax(mx[cc], fabs(v));
-        }
-        if (extra) ex += extra[i];
-        if (iextra) iex += (double)iextra[i];
-    }
-    for (int e = 0; e < 12; ++e) {
-        double v = e < 5 ? ss[e] : (e < 10 ? mx[e - 5] : (e == 10 ? ex : iex));
-        red[threadIdx.x] = v;
-        __syncthreads();
-        for (int st = 128; st > 0; st >>= 1) {
-            if ((int)threadIdx.x < st) {
-                if (e >= 5 && e < 10) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + st]);
-                else red[threadIdx.x] += red[threadIdx.x + st];
+// Per job (blockIdx.y): sums of squares and maxima per column of x [n][w],
+// the sums of extra [n] and of iextra [n_i].  part: [job][12][blocks].
+constexpr int ST_BLOCKS = 1024;
+
+__global__ __launch_bounds__(256) void k_stats_partial(StatJobs jobs, double* __restrict__ part) {
+    __shared__ double red[4][12];
+    const StatJob jb = jobs.job[blockIdx.y];
+    double v[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    const int64_t first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = first; i < jb.n; i += stride) {
+#pragma unroll
+        for (int cc = 0; cc < 5; ++cc)
+            if (cc < jb.w) {
+                const double x = jb.x[i * jb.w + cc];
+                v[cc] += x * x;
+                v[5 + cc] = fmax(v[5 + cc], fabs(x));
             }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) part[blockIdx.x * 12 + e] = red[0];
-        __syncthreads();
+        if (jb.extra) v[10] += jb.extra[i];
     }
+    for (int64_t i = first; i < jb.n_i; i += stride) v[11] += (double)jb.iextra[i];
+    const double s = block_sums<12, true>(v, red);
+    if (threadIdx.x < 12) part[((int64_t)blockIdx.y * 12 + threadIdx.x) * gridDim.x + blockIdx.x] = s;
 }
 
-__global__ void k_stats_final(const double* __restrict__ part, int64_t n, double* __restrict__ out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double v[12] = {0};
-    for (int b = 0; b < ST_BLOCKS; ++b)
-        for (int e = 0; e < 12; ++e) {
-            const double x = part[b * 12 + e];
-            if (e >= 5 && e < 10) v[e] = fmax(v[e], x);
-            else v[e] += x;
+// One block per job, one wavefront per value (in turn).  out: [job][12].
+__global__ __launch_bounds__(256) void k_stats_final(StatJobs jobs, int blocks, const double* __restrict__ part,
+                                                     double* __restrict__ out) {
+    const int lane = threadIdx.x & 63;
+    const int64_t n = jobs.job[blockIdx.x].n;
+    for (int e = threadIdx.x >> 6; e < 12; e += 4) {
+        const double* p = part + ((int64_t)blockIdx.x * 12 + e) * blocks;
+        const bool mx = e >= 5 && e < 10;
+        double v = 0.0;
+        for (int b = lane; b < blocks; b += 64) v = mx ? fmax(v, p[b]) : v + p[b];
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) {
+            const double o = __shfl_xor(v, m, 64);
+            v = mx ? fmax(v, o) : v + o;
         }
-    for (int e = 0; e < 5; ++e) out[e] = n > 0 ? sqrt(v[e] / (double)n) : 0.0;
-    for (int e = 5; e < 12; ++e) out[e] = v[e];
+        if (lane == 0) out[blockIdx.x * 12 + e] = e < 5 ? (n > 0 ? sqrt(v / (double)n) : 0.0) : v;
+    }
 }
 
 inline int grid_for(int64_t n, int threads = 256, int cap = 65536) {
@@ -365,12 +403,8 @@ void launch_prep_sources(agis_ctx* ctx) {
 
 
 
-void launch_apply_add(agis_ctx* ctx, int64_t n, double* x, const double* dx) {
-    if (n > 0) k_apply_add<<<grid_for(n), 256, 0, ctx->stream>>>(n, x, dx);
-}
-
-void launch_apply_attitude(agis_ctx* ctx) {
-    k_apply_add<<<grid_for(4 * ctx->N), 256, 0, ctx->stream>>>(4 * ctx->N, ctx->a, ctx->da);
+void launch_apply_add(agis_ctx* ctx, int64_t n, double* x, const double* dx, int64_t m, double* y, const double* dy) {
+    if (n + m > 0) k_apply_add<<<grid_for(n + m), 256, 0, ctx->stream>>>(n, x, dx, m, y, dy);
 }
 
 void launch_calib_solve(agis_ctx* ctx, double* rc) {
@@ -380,20 +414,15 @@ void launch_calib_solve(agis_ctx* ctx, double* rc) {
                                                            ctx->c, ctx->dc, rc);
 }
 
-void launch_apply_calibration(agis_ctx* ctx) {
-    k_apply_add<<<grid_for(ctx->n_cells), 256, 0, ctx->stream>>>(ctx->n_cells, ctx->c, ctx->dc);
-}
-
 void launch_frame_fit(agis_ctx* ctx) {
-    k_frame_fit_partial<<<FR_BLOCKS, 256, 0, ctx->stream>>>(ctx->k, ctx->n_src, ctx->s, ctx->s_ref, ctx->svar,
-                                                            ctx->red);
-    k_frame_fit_final<<<1, 64, 0, ctx->stream>>>(ctx->red, ctx->eo);
+    k_frame_fit_partial<<<FR_BLOCKS, 256, 0, ctx->stream>>>(ctx->n_src, ctx->s, ctx->s_ref, ctx->svar, ctx->red);
+    k_frame_fit_final<<<1, 1024, 0, ctx->stream>>>(ctx->k, ctx->red, ctx->eo);
 }
 
 void launch_frame_apply(agis_ctx* ctx) {
-    k_frame_apply_sources<<<grid_for(ctx->n_src), 256, 0, ctx->stream>>>(ctx->k, ctx->n_src, ctx->eo, ctx->s,
-                                                                         ctx->prep);
-    k_frame_apply_attitude<<<grid_for(ctx->N), 256, 0, ctx->stream>>>(ctx->k, ctx->N, ctx->eo, ctx->knots, ctx->a);
+    const int src_blocks = grid_for(ctx->n_src);
+    k_frame_apply<<<src_blocks + grid_for(ctx->N), 256, 0, ctx->stream>>>(
+        ctx->k, src_blocks, ctx->n_src, ctx->N, ctx->eo, ctx->s, ctx->prep, ctx->knots, ctx->a);
 }
 
 void launch_residuals(agis_ctx* ctx, double* R) {
@@ -404,10 +433,12 @@ void launch_residuals(agis_ctx* ctx, double* R) {
                                                                  ctx->knots, ctx->ktab, ctx->a, ctx->c, R);
 }
 
-void launch_stats(agis_ctx* ctx, const double* x, int64_t n, int w, const double* extra, const int32_t* iextra,
-                  double* out) {
-    k_stats_partial<<<ST_BLOCKS, 256, 0, ctx->stream>>>(x, n, w, extra, iextra, ctx->red);
-    k_stats_final<<<1, 64, 0, ctx->stream>>>(ctx->red, n, out);
+void launch_stats(agis_ctx* ctx, const StatJobs& jobs, int n_jobs, double* out) {
+    int64_t n = 1;
+    for (int j = 0; j < n_jobs; ++j) n = std::max(n, std::max(jobs.job[j].n, jobs.job[j].n_i));
+    const int blocks = grid_for(n, 256, ST_BLOCKS);
+    k_stats_partial<<<dim3(blocks, n_jobs), 256, 0, ctx->stream>>>(jobs, ctx->red);
+    k_stats_final<<<n_jobs, 256, 0, ctx->stream>>>(jobs, blocks, ctx->red, out);
 }
 
 }  // namespace agis
