@@ -52,6 +52,7 @@ struct StatJobs {
 
 struct Timers {
     hipEvent_t ev[10][2];
+    hipEvent_t beg[10], end[10];         // the events a block's time lies between (its own or a neighbour's)
     bool valid[10];
 };
 

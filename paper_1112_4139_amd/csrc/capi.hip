@@ -442,10 +442,11 @@ extern "C" int agis_create(const agis_config_t* cfg, agis_ctx_t** out) {
     }
     for (int e = 0; e < 10; ++e) {
         ctx->tm.valid[e] = false;
-        if (hipEventCreate(&ctx->tm.ev[e][0]) != hipSuccess || hipEventCreate(&ctx->tm.ev[e][1]) != hipSuccess) {
-            ctx->err = "hipEventCreate failed";
-            return fail(AGIS_E_DEVICE);
-        }
+        for (int k = 0; k < 2; ++k)
+            if (hipEventCreateWithFlags(&ctx->tm.ev[e][k], hipEventDisableSystemFence) != hipSuccess) {
+                ctx->err = "hipEventCreate failed";
+                return fail(AGIS_E_DEVICE);
+            }
     }
     *out = ctx;
     return AGIS_OK;
@@ -699,18 +700,28 @@ extern "C" int agis_get_calibration(agis_ctx_t* ctx, int64_t n, double* c, int w
 // --- timing and statistics helpers -----------------------------------------
 enum { T_S = 0, T_AC = 1, T_BAND = 2, T_CAL = 3, T_FRAME = 4, T_EPS = 5, T_ITER = 6 };
 
+// Times on the stream between events without a system fence (nothing but
+// their time is read).  A record costs a gap of about 4 us between two
+// kernels, so a block that follows another one directly starts at its stop
+// event (tfollow), and an iteration begins and ends with its blocks.
 static void tstart(agis_ctx* ctx, int e) {
-    if (ctx->timing) (void)hipEventRecord(ctx->tm.ev[e][0], ctx->stream);
+    if (!ctx->timing) return;
+    (void)hipEventRecord(ctx->tm.ev[e][0], ctx->stream);
+    ctx->tm.beg[e] = ctx->tm.ev[e][0];
+}
+static void tfollow(agis_ctx* ctx, int e, int prev) {
+    if (ctx->timing) ctx->tm.beg[e] = ctx->tm.ev[prev][1];
 }
 static void tstop(agis_ctx* ctx, int e) {
     if (!ctx->timing) return;
     (void)hipEventRecord(ctx->tm.ev[e][1], ctx->stream);
+    ctx->tm.end[e] = ctx->tm.ev[e][1];
     ctx->tm.valid[e] = true;
 }
 static double tget(agis_ctx* ctx, int e) {
     if (!ctx->tm.valid[e]) return 0.0;
     float ms = 0.0f;
-    if (hipEventElapsedTime(&ms, ctx->tm.ev[e][0], ctx->tm.ev[e][1]) != hipSuccess) return 0.0;
+    if (hipEventElapsedTime(&ms, ctx->tm.beg[e], ctx->tm.end[e]) != hipSuccess) return 0.0;
     return (double)ms;
 }
 
@@ -728,24 +739,28 @@ static int run_source(agis_ctx* ctx) {
 // see the same parameters (S[AC]).  apply = false leaves the updates in da
 // and dc; rc (optional) receives the calibration right-hand sides.
 static int run_ac(agis_ctx* ctx, bool do_a, bool do_c, bool eps_update = false, bool apply = true,
-                  double* rc = nullptr, bool do_g = false) {
+                  double* rc = nullptr, bool do_g = false, int after = -1) {
+    // after: the block that ended where this call begins (-1: none)
     if (eps_update && robust_now(ctx)) {
-        tstart(ctx, T_EPS);
+        if (after >= 0) tfollow(ctx, T_EPS, after);
+        else tstart(ctx, T_EPS);
         launch_excess_noise(ctx);
         tstop(ctx, T_EPS);
+        after = T_EPS;
     }
-    tstart(ctx, T_AC);
+    if (after >= 0) tfollow(ctx, T_AC, after);
+    else tstart(ctx, T_AC);
     launch_ac_pass(ctx);
     HIPCHK(hipGetLastError());
     tstop(ctx, T_AC);
     if (do_a) {
-        tstart(ctx, T_BAND);
+        tfollow(ctx, T_BAND, T_AC);
         launch_band_solve(ctx);
         HIPCHK(hipGetLastError());
         tstop(ctx, T_BAND);
     }
     if (do_c) {
-        tstart(ctx, T_CAL);
+        tfollow(ctx, T_CAL, do_a ? T_BAND : T_AC);
         if (ctx->geo_ccds > 0) launch_geo_solve(ctx);
         else launch_calib_solve(ctx, rc);
         HIPCHK(hipGetLastError());
@@ -939,11 +954,11 @@ extern "C" int agis_frame_apply(agis_ctx_t* ctx, const double eps_omega[6]) {
 // One S[AC] iteration followed by the frame rotation (Sect. 4.6, 6.1);
 // st (may be null) receives the block statistics.
 static int iterate_once(agis_ctx* ctx, agis_iter_stats_t* st) {
-    tstart(ctx, T_ITER);
     int rc = run_source(ctx);
     if (rc) return rc;
+    ctx->tm.beg[T_ITER] = ctx->tm.beg[T_S];
     // robust: eps_a from the residuals after the source update (Sect. 5.2.5)
-    rc = run_ac(ctx, true, true, true, true, nullptr, true);
+    rc = run_ac(ctx, true, true, true, true, nullptr, true, T_S);
     if (rc) return rc;
     if (ctx->have_ref) {
         tstart(ctx, T_FRAME);
@@ -951,8 +966,11 @@ static int iterate_once(agis_ctx* ctx, agis_iter_stats_t* st) {
         launch_frame_apply(ctx);
         HIPCHK(hipGetLastError());
         tstop(ctx, T_FRAME);
+        ctx->tm.end[T_ITER] = ctx->tm.end[T_FRAME];
+        ctx->tm.valid[T_ITER] = ctx->tm.valid[T_FRAME];
+    } else {
+        tstop(ctx, T_ITER);
     }
-    tstop(ctx, T_ITER);
     if (st) {
         if (ctx->have_ref) launch_copy(ctx, 6, ctx->eo, ctx->stat + 36);
         if ((rc = read_stats(ctx, &st->s, &st->a, &st->c))) return rc;
