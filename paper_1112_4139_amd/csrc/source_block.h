@@ -18,39 +18,53 @@ __device__ __forceinline__ void source_finish(const double acc[21], int64_t i, d
                                               double* __restrict__ qsrc, int32_t* __restrict__ sdef,
                                               double* __restrict__ svar, double* __restrict__ rhs = nullptr,
                                               double eps_i2 = 0.0) {
-    double U[25], N[25], x[5];
-    int e = 0;
-    for (int rr = 0; rr < 5; ++rr)
-        for (int cc = rr; cc < 5; ++cc) {
-            U[rr * 5 + cc] = acc[e];
-            N[rr * 5 + cc] = acc[e];
-            N[cc * 5 + rr] = acc[e];
-            ++e;
-        }
+    double U[25], x[5];
+    {
+        int e = 0;
+#pragma unroll
+        for (int rr = 0; rr < 5; ++rr)
+#pragma unroll
+            for (int cc = rr; cc < 5; ++cc) U[rr * 5 + cc] = acc[e++];
+    }
+#pragma unroll
     for (int rr = 0; rr < 5; ++rr) x[rr] = acc[15 + rr];
     if (rhs)
+#pragma unroll
         for (int rr = 0; rr < 5; ++rr) rhs[5 * i + rr] = acc[15 + rr];
     const int d = small_chol_factor<5>(U);
     small_chol_subst<5>(U, x);
-    // diagonal of the inverse normal matrix, the first-order variances of
-    // the five parameters (Sect. 5.1.1): C2 and C3 on the unit vectors
+    // diagonal of the inverse normal matrix V V', V = U^-1 (upper triangular,
+    // row by row from its last), the first-order variances of the five
+    // parameters (Sect. 5.1.1)
+    double V[25];
 #pragma unroll
-    for (int kk = 0; kk < 5; ++kk) {
-        double ev[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-        ev[kk] = 1.0;
-        small_chol_subst<5>(U, ev);
-        svar[5 * i + kk] = d > 0 ? 0.0 : ev[kk];
+    for (int kk = 4; kk >= 0; --kk) {
+        V[kk * 5 + kk] = U[kk * 5 + kk];
+        double sum = V[kk * 5 + kk] * V[kk * 5 + kk];
+#pragma unroll
+        for (int cc = kk + 1; cc < 5; ++cc) {
+            double t = 0.0;
+#pragma unroll
+            for (int m = kk + 1; m <= cc; ++m) t += U[kk * 5 + m] * V[m * 5 + cc];
+            V[kk * 5 + cc] = -t * U[kk * 5 + kk];
+            sum += V[kk * 5 + cc] * V[kk * 5 + cc];
+        }
+        svar[5 * i + kk] = d > 0 ? 0.0 : sum;
     }
     // Q_i = h'Wh - 2 d'b + d'N d (eq:Qi)
     double dNd = 0.0, db = 0.0;
-    for (int rr = 0; rr < 5; ++rr) {
-        double t = 0.0;
-        for (int cc = 0; cc < 5; ++cc) t += N[rr * 5 + cc] * x[cc];
-        dNd += x[rr] * t;
-        db += x[rr] * acc[15 + rr];
+    {
+        int e = 0;
+#pragma unroll
+        for (int rr = 0; rr < 5; ++rr) {
+#pragma unroll
+            for (int cc = rr; cc < 5; ++cc, ++e) dNd += (cc == rr ? 1.0 : 2.0) * acc[e] * x[rr] * x[cc];
+            db += x[rr] * acc[15 + rr];
+        }
     }
     qsrc[i] = acc[20] - 2.0 * db + dNd;
     sdef[i] = d;
+#pragma unroll
     for (int rr = 0; rr < 5; ++rr) ds[5 * i + rr] = x[rr];
     const double na = alpha + x[0] / cd, nd = delta + x[1];
     const double npl = plx + x[2], npa = pma + x[3], npd = pmd + x[4];
@@ -86,10 +100,26 @@ __device__ __forceinline__ double down_weight(double z) {
     return exp(-a / 3.0);
 }
 
+// Value of v in another lane of the 16-lane row (DPP pattern CTRL).
+template <int CTRL>
+__device__ __forceinline__ double row_move(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+
+// Sum over groups of G neighbouring lanes (every lane of the group gets it):
+// within a 16-lane row by register moves (mirrored row, mirrored half row,
+// swapped pairs, swapped lanes), across rows through LDS permutes.
 template <int G>
 __device__ __forceinline__ double group_sum(double v) {
-#pragma unroll
-    for (int m = G / 2; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+    if constexpr (G >= 64) v += __shfl_xor(v, 32, 64);
+    if constexpr (G >= 32) v += __shfl_xor(v, 16, 64);
+    if constexpr (G >= 16) v += row_move<0x140>(v);
+    if constexpr (G >= 8) v += row_move<0x141>(v);
+    if constexpr (G >= 4) v += row_move<0x4E>(v);
+    if constexpr (G >= 2) v += row_move<0xB1>(v);
     return v;
 }
 
