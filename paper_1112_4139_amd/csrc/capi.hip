@@ -344,6 +344,11 @@ extern "C" int agis_create(const agis_config_t* cfg, agis_ctx_t** out) {
     k.eph_Lrate = cfg->eph_Lrate;
     k.cos_obl = std::cos(cfg->eps_obl);
     k.sin_obl = std::sin(cfg->eps_obl);
+    k.au_r = k.au_c * k.eph_r;
+    k.vel = k.eph_r * k.eph_Lrate * k.au_c;
+    k.vel_co = k.vel * k.cos_obl;
+    k.vel_so = k.vel * k.sin_obl;
+    k.one_vel2 = 1.0 + k.vel * k.vel;
     k.cos_half_gamma = std::cos(k.gamma_half);
     k.sin_half_gamma = std::sin(k.gamma_half);
     k.half_gamma_err = (double)((long double)k.gamma_half -
@@ -354,6 +359,7 @@ extern "C" int agis_create(const agis_config_t* cfg, agis_ctx_t** out) {
     if (cfg->robust) {
         ctx->n_buckets = (ctx->K + cfg->eps_bucket - 1) / cfg->eps_bucket;
         k.n_buckets = ctx->n_buckets;
+        k.inv_bucket = 1.0 / cfg->eps_bucket;
     }
     if (const char* e = std::getenv("AGIS_S_GROUP")) ctx->s_group = std::atoi(e);
     if (const char* e = std::getenv("AGIS_SELECT_REG_LIMIT")) ctx->select_reg_limit = std::atoll(e);

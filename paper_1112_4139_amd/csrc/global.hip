@@ -47,7 +47,7 @@ __global__ __launch_bounds__(64) void k_g_pass(DevConsts k, int64_t K, const int
         if (robust) {
             // the A/C weight (eq:W): sigma~^2 of the record's component and
             // bucket, plus eps_i^2 in robust mode 2
-            const double s2 = sg * sg + eps_a2[eps_slot(k, cf, j, eps_bucket)] + (robust == 2 ? sp.pad : 0.0);
+            const double s2 = sg * sg + eps_a2[eps_slot(k, cf, j)] + (robust == 2 ? sp.pad : 0.0);
             W = down_weight(o.R / sqrt(s2)) / s2;
         } else {
             W = rcp_nr(sg * sg);

@@ -55,8 +55,8 @@ __global__ __launch_bounds__(256, 2) void k_source_update(DevConsts k, int64_t n
                                                        const SigT* __restrict__ osig,
                                                        const int32_t* __restrict__ ocell,
                                                        const int32_t* __restrict__ oell,
-                                                       const double* __restrict__ knots,
-                                                       const KnotTab* __restrict__ ktab, const double* __restrict__ a,
+                                                       const double* __restrict__ knots, const KnotTab* __restrict__ ktab,
+                                                       const double* __restrict__ a,
                                                        const double* __restrict__ c, double* __restrict__ s,
                                                        SrcPrep* __restrict__ prep, double* __restrict__ ds,
                                                        double* __restrict__ qsrc, int32_t* __restrict__ sdef,
@@ -64,33 +64,36 @@ __global__ __launch_bounds__(256, 2) void k_source_update(DevConsts k, int64_t n
                                                        double* __restrict__ rhs) {
     constexpr int GPB = 256 / G;
     __shared__ double pool[GPB][23];
+    __shared__ __align__(16) char stage[4][STAGE_BYTES];
     const int gl = threadIdx.x % G;
     // group k takes the k-th source of the launch order
-    const int64_t kg = (int64_t)blockIdx.x * GPB + threadIdx.x / G;
+    const int64_t kb = (int64_t)blockIdx.x * GPB;
+    const int64_t kg = kb + threadIdx.x / G;
     const bool valid = kg < n_src;
-    const int64_t i = valid ? order[kg] : 0;
-    double alpha = 0.0, delta = 0.0, plx = 0.0, pma = 0.0, pmd = 0.0;
+    SourceDir sd;
     int64_t l0 = 0, l1 = 0;
-    if (valid) {
-        const double* si = s + 5 * i;
-        alpha = si[0];
-        delta = si[1];
-        plx = si[2];
-        pma = si[3];
-        pmd = si[4];
-        l0 = off[i];
-        l1 = off[i + 1];
+    double cd;
+    ObsStream<SigT> st{ot, oeta, osig, ocell, oell, a, knots, ktab, c, nullptr, stage[threadIdx.x >> 6]};
+    int trips, mine;                     // the wavefront's and this lane's records
+    {
+        double alpha = 0.0, delta = 0.0, plx = 0.0, pma = 0.0, pmd = 0.0;
+        if (valid) {
+            const int64_t i = order[kg];
+            l0 = off[i];
+            l1 = off[i + 1];
+            const double* si = s + 5 * i;
+            alpha = si[0];
+            delta = si[1];
+            plx = si[2];
+            pma = si[3];
+            pmd = si[4];
+        }
+        trips = wave_trips<G>(l0, l1);
+        mine = (int)(l1 - l0 - gl + G - 1) / G;
+        if (trips > 0) st.start(l0 + gl, l1, G);
+        cd = source_dir(k, alpha, delta, plx, pma, pmd, sd);
+        if (trips > 0) st.gather(k, 0);
     }
-    double sa, ca, sd, cd;
-    sincos(alpha, &sa, &ca);
-    sincos(delta, &sd, &cd);
-    const double p[3] = {-sa, ca, 0.0};
-    const double q[3] = {-sd * ca, -sd * sa, cd};
-    const double r[3] = {cd * ca, cd * sa, sd};
-    double mu[3];
-#pragma unroll
-    for (int cc = 0; cc < 3; ++cc) mu[cc] = p[cc] * pma + q[cc] * pmd;
-
     double acc[21];
 #pragma unroll
     for (int e = 0; e < 21; ++e) acc[e] = 0.0;
@@ -101,50 +104,16 @@ __global__ __launch_bounds__(256, 2) void k_source_update(DevConsts k, int64_t n
     float fs[MIXED ? 15 : 1], fc[MIXED ? 15 : 1];
 #pragma unroll
     for (int e = 0; e < (MIXED ? 15 : 1); ++e) fs[e] = fc[e] = 0.0f;
-    int64_t l = l0 + gl;
-    // Current observation: columns, and the gathered attitude coefficients,
-    // interval table entry and calibration of its cell.  The next
-    // observation's columns load at the top of an iteration, its gathers
-    // after the current observation has been evaluated.
-    double t_c = 0.0, e_c = 0.0, cal_c = 0.0;
-    SigT s_c = 1;
-    int32_t ell_c = 3;
-    bool ac_c = false;
-    double a_c[16];
-    KnotTab kt_c = {0.0, 1.0, 0.0, 0.0};
-#pragma unroll
-    for (int e = 0; e < 16; ++e) a_c[e] = 0.0;
-    if (l < l1) {
-        t_c = ot[l];
-        e_c = oeta[l];
-        s_c = osig[l];
-        ell_c = oell[l];
-        const int32_t cf = ocell[l];
-        cal_c = c[cf >> 1];
-        ac_c = AC && cf >= k.ac_cf0;
-        const double* a4 = a + 4 * (ell_c - 3);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) a_c[e] = a4[e];
-        kt_c = ktab[ell_c - 3];
-    }
-    for (; l < l1; l += G) {
-        const int64_t ln = l + G;
-        const bool more = ln < l1;
-        double t_n = 0.0, e_n = 0.0;
-        SigT s_n = 1;
-        int32_t c_n = 0, ell_n = 3;
-        if (more) {
-            t_n = ot[ln];
-            e_n = oeta[ln];
-            s_n = osig[ln];
-            c_n = ocell[ln];
-            ell_n = oell[ln];
-        }
-        ObsEval o;
-        observe<DEFL>(k, t_c, e_c, cal_c, r, mu, plx, a_c, knots + (ell_c - 2), kt_c, o, ac_c);
-        double A[5];
-        source_partials(o, p, q, r, A, ac_c);
-        const double sg = (double)s_c;
+    auto record = [&](int u, int at) {
+        double qa[4], sL, cL;
+        st.take(k, u, qa, sL, cL);
+        const double t = st.t[u], obs = st.e[u] + st.cal;
+        const bool ac = AC && st.cf[u] >= k.ac_cf0;
+        const double sg = (double)st.s[u];
+        st.advance(k, u);
+        if (at >= mine) return;
+        double A[5], R, tau;
+        source_row<AC, DEFL>(k, sd, qa, sL, cL, t - k.t_ep, obs, ac, A, R, tau);
         const double W = rcp_nr(sg * sg);
         if constexpr (MIXED) {
             float Af[5];
@@ -161,32 +130,24 @@ __global__ __launch_bounds__(256, 2) void k_source_update(DevConsts k, int64_t n
                     ++e;
                 }
             }
+        }
+        int e = 0;
 #pragma unroll
-            for (int rr = 0; rr < 5; ++rr) acc[15 + rr] += W * A[rr] * o.R;
-            acc[20] += W * o.R * o.R;
-        } else {
-            int e = 0;
-#pragma unroll
-            for (int rr = 0; rr < 5; ++rr) {
-                const double wa = W * A[rr];
+        for (int rr = 0; rr < 5; ++rr) {
+            const double wa = W * A[rr];
+            if constexpr (!MIXED) {
 #pragma unroll
                 for (int cc = rr; cc < 5; ++cc) acc[e++] += wa * A[cc];
             }
-#pragma unroll
-            for (int rr = 0; rr < 5; ++rr) acc[15 + rr] += W * A[rr] * o.R;
-            acc[20] += W * o.R * o.R;
+            acc[15 + rr] += wa * R;
         }
-        t_c = t_n;
-        e_c = e_n;
-        s_c = s_n;
-        ell_c = ell_n;
-        if (more) {
-            cal_c = c[c_n >> 1];
-            ac_c = AC && c_n >= k.ac_cf0;
-            const double* a4 = a + 4 * (ell_n - 3);
+        acc[20] += W * R * R;
+    };
+    for (int it = 0; it < trips; it += OBS_AHEAD) {
 #pragma unroll
-            for (int e2 = 0; e2 < 16; ++e2) a_c[e2] = a4[e2];
-            kt_c = ktab[ell_n - 3];
+        for (int u = 0; u < OBS_AHEAD; ++u) {
+            if (it + u >= trips) break;
+            record(u, it + u);
         }
     }
     if constexpr (MIXED) {
@@ -206,7 +167,7 @@ __global__ __launch_bounds__(256, 2) void k_source_update(DevConsts k, int64_t n
     }
     __syncthreads();
     if (threadIdx.x >= GPB) return;
-    const int64_t kf = (int64_t)blockIdx.x * GPB + threadIdx.x;
+    const int64_t kf = kb + threadIdx.x;
     if (kf >= n_src) return;
     const int64_t fi = order[kf];
     double sum[21];
@@ -331,7 +292,7 @@ __global__ __launch_bounds__(64 * AC_WAVES) void k_ac_pass(DevConsts k, int64_t 
             double W;
             if (robust) {
                 // robust mode 2: plus the source's excess noise eps_i^2 (eq:W)
-                const double s2 = sg * sg + eps_a2[eps_slot(k, cf_c, j, eps_bucket)] + (robust == 2 ? sp_c.pad : 0.0);
+                const double s2 = sg * sg + eps_a2[eps_slot(k, cf_c, j)] + (robust == 2 ? sp_c.pad : 0.0);
                 W = h_c ? down_weight(o.R / sqrt(s2)) / s2 : 0.0;
             } else {
                 W = h_c ? rcp_nr(sg * sg) : 0.0;

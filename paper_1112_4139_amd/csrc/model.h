@@ -27,15 +27,21 @@ struct DevConsts {
     int64_t n_buckets;                       // excess-noise buckets per component (robust)
     double defl;                             // 0, or GM_sun / (c^2 AU) [rad AU]: the Sun's light deflection
     const double* gpar;                      // device [2]: g0 (gamma = 1 + g0), g1 (held at zero)
+    // products of the ephemeris constants: radius in light time [s], orbital
+    // speed over c and its components' factors, 1 + (speed / c)^2
+    double au_r, vel, vel_co, vel_so, one_vel2;
+    double inv_bucket;                       // 1 / (knot intervals per excess-noise bucket) (robust)
 };
 
 // Slot in the excess attitude noise array of a record with cell/fov code
 // cf in knot interval j: the component (0 along scan, 1 across scan in the
 // preceding, 2 in the following field of view) times the buckets per
 // component, plus the interval's bucket.
-__device__ __forceinline__ int64_t eps_slot(const DevConsts& k, int32_t cf, int64_t j, int eps_bucket) {
+// (a product with the reciprocal: (j + 1/2) / eps_bucket is at least 1 / (2
+// eps_bucket) from an integer, far above its rounding).
+__device__ __forceinline__ int64_t eps_slot(const DevConsts& k, int32_t cf, int64_t j) {
     const int64_t comp = cf >= k.ac_cf0 ? 1 + (cf & 1) : 0;
-    return comp * k.n_buckets + j / eps_bucket;
+    return comp * k.n_buckets + (int64_t)(int32_t)(((double)(int32_t)j + 0.5) * k.inv_bucket);
 }
 
 // Source data gathered per observation by the time-ordered pass: barycentric
@@ -363,6 +369,174 @@ __device__ __forceinline__ void global_partials(const ObsEval& o, const double r
     for (int c = 0; c < 3; ++c) dpl[c] = -(o.b[c] - r[c] * rb);
     a_plx = (f * dot3(m, dpl) - mu_ * dot3(o.vc, dpl)) * secz;
     a_g0 = (f * dot3(m, o.dudg) - mu_ * dot3(o.vc, o.dudg)) * secz;
+}
+
+// The library functions that observations in range never need, kept out of
+// line: inlined, their constants and temporaries cost the S pass a third of
+// its registers.
+__device__ __attribute__((noinline)) inline double far_angle(double y, double x) { return atan2(y, x); }
+__device__ __attribute__((noinline)) inline double2 far_orbit(double L) {
+    double2 o;
+    sincos(L, &o.x, &o.y);
+    return o;
+}
+
+// One source's data in the form source_row() takes: direction, proper-motion
+// vector, the triad's p (p_z = 0) and q, parallax times the orbit's radius.
+struct SourceDir {
+    double r[3], mu[3], p0, p1, q[3], plx_r;
+};
+
+__device__ __forceinline__ double copysign_of(double mag, double sgn) { return __builtin_copysign(mag, sgn); }
+
+// Sine and cosine of the observer's orbital longitude d past the interval's
+// start (Taylor series to d^6 for |d| < 1e-2, as in observe()).
+__device__ __forceinline__ void orbit_at(const DevConsts& k, const KnotTab& kt, double dt, double t, double& sL,
+                                         double& cL) {
+    const double d = k.eph_Lrate * dt;
+    if (__builtin_expect(fabs(d) < 1e-2, 1)) {
+        const double d2 = d * d;
+        const double sd = d * (1.0 - d2 * (1.0 / 6.0 - d2 * (1.0 / 120.0)));
+        const double cd = 1.0 - d2 * (0.5 - d2 * (1.0 / 24.0 - d2 * (1.0 / 720.0)));
+        sL = kt.sL * cd + kt.cL * sd;
+        cL = kt.cL * cd - kt.sL * sd;
+    } else {
+        const double2 o = far_orbit(k.eph_L0 + k.eph_Lrate * t);
+        sL = o.x;
+        cL = o.y;
+    }
+}
+
+// Residual and design row -dR/ds of one observation for the S block: the
+// model of observe() and source_partials(), in a form that forms neither unit
+// vector nor unit quaternion.  qa: any multiple of the attitude quaternion
+// (sum a_n B_n as it is); sL, cL: the observer's orbital longitude; tt: t -
+// t_ep; obs: eta_obs (zeta_obs) plus the calibration.
+//  * The field angle needs the ratio of two components of M uu only (M =
+//    |q|^2 A, uu = ubar + v_G/c), for which lengths cancel: no third row of M
+//    along scan, no normalisation.
+//  * With S = M uu, m^ = M'(-S_y, S_x, 0) is |q|^2 rho_S times the AL unit
+//    vector m, and the design entry (f m.d - (m.ubar)(v.d)) sec zeta becomes
+//    (f m^.d - (m^.ubar)(v.d)) |uu| / rho_S^2; m is normal to uu, so m.ubar =
+//    -m.v (not with the deflection's term in uu); v.b = 0 on the circular
+//    orbit.  1/rho_S^2 comes from the reciprocal that the angle's quotient
+//    took (1 + z^2 in series for |z| < 1e-2).  Across scan M'(-S_x S_z, -S_y
+//    S_z, rho_S^2) is |q|^2 rho_S |S| n, and the factor |uu| / (rho_S |S|^2).
+// About 190 FP64 instructions along scan, 300 before; two reciprocal square
+// roots and one reciprocal.
+template <bool AC, bool DEFL>
+__device__ __forceinline__ void source_row(const DevConsts& k, const SourceDir& s, const double qa[4], double sL,
+                                           double cL, double tt, double obs, bool ac, double A[5], double& R,
+                                           double& tau) {
+    const double b[3] = {cL, k.cos_obl * sL, k.sin_obl * sL};          // in units of the orbit's radius
+    const double v[3] = {-k.vel * sL, k.vel_co * cL, k.vel_so * cL};
+    const double rb = dot3(s.r, b);
+    tau = (rb * k.au_r + tt) * k.inv_year;
+    double ub[3], uu[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) ub[c] = s.r[c] + tau * s.mu[c] - s.plx_r * b[c];
+    const double iub = rsqrt_nr(dot3(ub, ub));
+    const double bv = dot3(ub, v) * iub;
+    const double f = 1.0 - bv;
+    double uu2;
+    if constexpr (DEFL) {
+        // the Sun's light deflection, as in observe()
+        const double rad = k.eph_r;
+        const double ib = rsqrt_nr(rad * rad * dot3(b, b));
+        const double eu = dot3(b, ub) * (rad * ib * iub);
+        const double g = k.defl * ib / (1.0 + eu) * (2.0 + k.gpar[0]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) uu[c] = ub[c] * iub + g * (b[c] * (rad * ib) - eu * ub[c] * iub) + v[c];
+        uu2 = dot3(uu, uu);
+    } else {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) uu[c] = ub[c] * iub + v[c];
+        uu2 = k.one_vel2 + 2.0 * bv;
+    }
+    const double nuu = uu2 * rsqrt_nr(uu2);
+    // |q|^2 times the attitude matrix, its first two rows (the third across scan)
+    const double x = qa[0], y = qa[1], z = qa[2], w = qa[3];
+    const double x2 = x + x, y2 = y + y, z2 = z + z;
+    const double al = w * w - z * z, be = x * x - y * y, xy = x2 * y;
+    const double M0[3] = {al + be, xy + z2 * w, x2 * z - y2 * w};
+    const double M1[3] = {xy - z2 * w, al - be, y2 * z + x2 * w};
+    const double S0 = dot3(M0, uu), S1 = dot3(M1, uu);
+    double m[3], kap;
+    if (AC && ac) {
+        const double M2[3] = {x2 * z + y2 * w, y2 * z - x2 * w, (w * w + z * z) - (x * x + y * y)};
+        const double S2 = dot3(M2, uu);
+        const double rho2 = S0 * S0 + S1 * S1;
+        const double irho = rsqrt_nr(rho2);
+        const double q = S2 * irho, q2 = q * q;
+        const double zeta = fabs(q) < 1e-2
+                                ? q * (1.0 + q2 * (-1.0 / 3.0 + q2 * (1.0 / 5.0 + q2 * (-1.0 / 7.0 + q2 * (1.0 / 9.0)))))
+                                : far_angle(S2, rho2 * irho);
+        R = obs - zeta;
+        const double n0 = -S2 * S0, n1 = -S2 * S1;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) m[c] = M0[c] * n0 + M1[c] * n1 + M2[c] * rho2;
+        kap = nuu * irho * rcp_nr(rho2 + S2 * S2);
+    } else {
+        // eta = phi - f Gamma_c / 2 with f = sign(phi): rotate (x, y) by -f Gamma_c/2
+        const double sg = copysign_of(k.sin_half_gamma, S1);
+        const double xr = S0 * k.cos_half_gamma + S1 * sg;
+        const double yr = S1 * k.cos_half_gamma - S0 * sg;
+        if (__builtin_expect(xr > 0.0 && fabs(yr) < 1e-2 * xr, 1)) {
+            const double ix = rcp_nr(xr);
+            const double q = yr * ix, q2 = q * q;
+            const double eta = q + q * (q2 * (-1.0 / 3.0 + q2 * (1.0 / 5.0 + q2 * (-1.0 / 7.0 + q2 * (1.0 / 9.0)))));
+            R = obs - eta + copysign_of(k.half_gamma_err, S1);
+            kap = nuu * (ix * ix) * (1.0 - q2 * (1.0 - q2 * (1.0 - q2)));
+        } else {
+            const double phi = far_angle(S1, S0);
+            R = obs - (phi >= 0.0 ? phi - k.gamma_half : phi + k.gamma_half);
+            kap = nuu * rcp_nr(S0 * S0 + S1 * S1);
+        }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) m[c] = M1[c] * S0 - M0[c] * S1;
+    }
+    const double mv = dot3(m, v);
+    const double mu_ = DEFL ? dot3(m, ub) * iub : -mv;
+    const double vp = v[0] * s.p0 + v[1] * s.p1;
+    const double mp = m[0] * s.p0 + m[1] * s.p1;
+    A[0] = (f * mp - mu_ * vp) * kap;
+    A[1] = (f * dot3(m, s.q) - mu_ * dot3(v, s.q)) * kap;
+    A[2] = (f * (rb * dot3(m, s.r) - dot3(m, b)) - mu_ * (rb * dot3(v, s.r))) * (kap * k.eph_r);
+    A[3] = A[0] * tau;
+    A[4] = A[1] * tau;
+}
+
+typedef double double4v __attribute__((ext_vector_type(4)));
+__device__ __attribute__((noinline)) inline double4v far_spline(const double* __restrict__ kn, double t) {
+    double B[4];
+    bspline4(kn, t, B);
+    return double4v{B[0], B[1], B[2], B[3]};
+}
+
+// The spline quaternion at t = tau_l + dt from the interval's coefficients a4
+// (x, y, z, w of four knots); kn: tau_{l-2..l+3}, read only when they are not
+// equally spaced.  From the second coefficient by differences, which are small:
+// the sum is rounded once, and so are the B-splines (1 - their sum for the
+// second) only to no effect.
+__device__ __forceinline__ void attitude_at(const double a4[16], const KnotTab& kt, double dt,
+                                            const double* __restrict__ kn, double t, double q[4]) {
+    double b0, b2, b3;
+    if (__builtin_expect(kt.inv_dt > 0.0, 1)) {
+        const double u = dt * kt.inv_dt, w = 1.0 - u, w2 = w * w;
+        b0 = w2 * w * (1.0 / 6.0);
+        b2 = 2.0 / 3.0 - 0.5 * (w2 * (1.0 + u));
+        b3 = u * u * u * (1.0 / 6.0);
+    } else {
+        const double4v b = far_spline(kn, t);
+        b0 = b.x;
+        b2 = b.z;
+        b3 = b.w;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const double a1 = a4[4 + c];
+        q[c] = a1 + (b0 * (a4[c] - a1) + (b2 * (a4[8 + c] - a1) + b3 * (a4[12 + c] - a1)));
+    }
 }
 
 // dR/dq = 2 sec(zeta) q {S'n, 0} (eq:dfadq), n of eq:srspqr; across scan
