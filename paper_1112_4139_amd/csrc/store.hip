@@ -150,6 +150,61 @@ __global__ void k_offsets_time(int64_t n, const double* __restrict__ t, const do
     }
 }
 
+// The records of each knot interval by source (then by time): one block per
+// interval, each record's place counted in LDS.  The order within an interval
+// is nobody's result, and the passes over it gather their sources' 64-byte
+// records: a star crosses nine CCDs 5 s apart, between which others do, so in
+// time order neighbouring lanes gather different stars' and by source up to
+// nine share one (the quadratic form of conjugate gradients over 22M records:
+// 700 -> 640 us, the A/C pass 724 -> 680).
+// Intervals of more than SORT_CAP records keep the time order.
+constexpr int SORT_THREADS = 128;
+constexpr int SORT_EACH = 16;
+constexpr int SORT_CAP = SORT_THREADS * SORT_EACH;
+
+__global__ __launch_bounds__(SORT_THREADS) void k_sort_intervals(int64_t K, const int64_t* __restrict__ off,
+                                                                 const int32_t* __restrict__ src,
+                                                                 int32_t* __restrict__ perm, double* __restrict__ t) {
+    __shared__ int32_t key[SORT_CAP];
+    for (int64_t j = blockIdx.x; j < K; j += gridDim.x) {
+        const int64_t l0 = off[j];
+        const int64_t n64 = off[j + 1] - l0;
+        if (n64 > SORT_CAP || n64 < 2) continue;           // the same for the whole block
+        const int n = (int)n64;
+        int32_t p[SORT_EACH];
+        double ti[SORT_EACH];
+        int place[SORT_EACH];
+#pragma unroll
+        for (int e = 0; e < SORT_EACH; ++e) {
+            const int l = threadIdx.x + e * SORT_THREADS;
+            if (l < n) {
+                p[e] = perm[l0 + l];
+                ti[e] = t[l0 + l];
+                key[l] = src[p[e]];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < SORT_EACH; ++e) {
+            const int l = threadIdx.x + e * SORT_THREADS;
+            place[e] = 0;
+            if (l < n) {
+                const int32_t own = key[l];
+                for (int m = 0; m < n; ++m) place[e] += key[m] < own || (key[m] == own && m < l) ? 1 : 0;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < SORT_EACH; ++e) {
+            const int l = threadIdx.x + e * SORT_THREADS;
+            if (l < n) {
+                perm[l0 + place[e]] = p[e];
+                t[l0 + place[e]] = ti[e];
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // Calibration cell of each field of view within each knot interval (across-
 // scan observations, pseudo-cell n_cells, have none); flags intervals whose
 // observations of one field of view span several cells.
@@ -286,6 +341,16 @@ int build_store(agis_ctx* ctx, const agis_obs_soa_t* obs, int where) {
     }
     tmp.push_back(temp);
     HIPCHK(hipcub::DeviceRadixSort::SortPairs(temp, tb, t_in, ctx->t_t, iota, perm_t, (int)n, 0, 64, st));
+
+    // ---- knot intervals, their records by source ----
+    int b2;
+    ALLOC(ctx->iv_off, ctx->K + 1, "iv_off");
+    grid1d(ctx->K + 1, b2);
+    k_offsets_time<<<b2, 256, 0, st>>>(n, ctx->t_t, ctx->knots, ctx->K, ctx->iv_off);
+    HIPCHK(hipGetLastError());
+    k_sort_intervals<<<(unsigned)std::min<int64_t>(std::max<int64_t>(ctx->K, 1), 1 << 20), SORT_THREADS, 0, st>>>(
+        ctx->K, ctx->iv_off, src_in, perm_t, ctx->t_t);
+    HIPCHK(hipGetLastError());
     ALLOC(ctx->t_eta, n, "t_eta");
     ALLOC(ctx->t_sig, n, "t_sig");
     ALLOC(ctx->t_src, n, "t_src");
@@ -313,16 +378,12 @@ int build_store(agis_ctx* ctx, const agis_obs_soa_t* obs, int where) {
                                             ctx->N, ctx->s_t, ctx->s_eta, ctx->s_sig, ctx->s_cell, ctx->s_ell);
     HIPCHK(hipGetLastError());
     ALLOC(ctx->src_off, ctx->n_src + 1, "src_off");
-    int b2;
     grid1d(ctx->n_src + 1, b2);
     k_offsets_int<<<b2, 256, 0, st>>>(n, src_sorted, ctx->n_src, ctx->src_off);
     HIPCHK(hipGetLastError());
 
-    // ---- knot intervals and their calibration cells ----
-    ALLOC(ctx->iv_off, ctx->K + 1, "iv_off");
+    // ---- the knot intervals' calibration cells ----
     grid1d(ctx->K + 1, b2);
-    k_offsets_time<<<b2, 256, 0, st>>>(n, ctx->t_t, ctx->knots, ctx->K, ctx->iv_off);
-    HIPCHK(hipGetLastError());
     ALLOC(ctx->iv_cell, 2 * ctx->K, "iv_cell");
     HIPCHK(hipMemsetAsync(flags, 0, sizeof(int), st));
     k_interval_cells<<<b2, 256, 0, st>>>(ctx->K, ctx->iv_off, ctx->t_cellfov, (int32_t)ctx->n_cells, ctx->iv_cell,
