@@ -28,6 +28,9 @@ constexpr int IV_SUMS = IV_PAIRS * 10 + 16;
 // calibration partial sums per interval: (sum W, sum W R) for fov +1 and -1
 constexpr int IV_CAL = 4;
 
+// Stride of the robust S block's columns: whole 128-byte lines.
+inline int64_t col_stride(int64_t n_obs) { return (n_obs + 15) & ~int64_t(15); }
+
 // A class of sources of the robust S block handled by the one-kernel path:
 // positions [k0, k1) of the count-ordered launch, each with at most cap
 // observations, blocks of nt threads.
@@ -171,7 +174,7 @@ struct agis_ctx {
     double* vs = nullptr;                // [n_src][2]: along, across scan
     double* src_eps2 = nullptr;          // [n_src] robust mode 2: excess source noise eps_i^2 of the last S update
     double* src_D = nullptr;             // [n_src] ... and its significance D
-    double* rcol = nullptr;              // [6][n_obs] (only when some source or bucket needs the HBM path)
+    double* rcol = nullptr;              // [6][col_stride(n_obs)] (only when some source or bucket needs the HBM path)
     // one-kernel robust paths (robust mode 1): the classes of the S block,
     // the leading launch positions that keep the three-kernel path (more
     // observations than the LDS holds), and whether the excess-noise

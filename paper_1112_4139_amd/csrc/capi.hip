@@ -560,7 +560,7 @@ extern "C" int agis_load_observations(agis_ctx_t* ctx, const agis_obs_soa_t* obs
             if (prc != AGIS_OK) return prc;
         }
         if (ctx->cfg.robust && need_columns)
-            ALLOC(ctx->rcol, 6 * std::max<int64_t>(ctx->n_obs, 1), "robust columns");
+            ALLOC(ctx->rcol, 6 * col_stride(std::max<int64_t>(ctx->n_obs, 1)), "robust columns");
     }
     if (ctx->cfg.robust) {
         // the inner iteration's by-source columns (A, h, sigma~^2), also

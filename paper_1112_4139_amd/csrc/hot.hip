@@ -8,7 +8,7 @@
 //                       runs Algorithms C1-C3 on the 5x5 system and applies
 //                       the update.
 //   k_ac_pass           A/C accumulation (Sect. 5.2.1, 5.2.4, 5.3).  One
-//                       wavefront per knot interval streams the time-ordered
+//                       wavefront per eight knot intervals streams the time-ordered
 //                       store at (s^(k+1), a^(k), c^(k)) and sums, on the FP64
 //                       matrix cores, the 10 block pairs x 10 unique entries
 //                       of eq:normAmod, its 16 right-hand-side entries and the
@@ -55,45 +55,41 @@ __global__ __launch_bounds__(256, 2) void k_source_update(DevConsts k, int64_t n
                                                        const SigT* __restrict__ osig,
                                                        const int32_t* __restrict__ ocell,
                                                        const int32_t* __restrict__ oell,
-                                                       const double* __restrict__ knots, const KnotTab* __restrict__ ktab,
-                                                       const double* __restrict__ a,
+                                                       const double* __restrict__ knots,
+                                                       const KnotTab* __restrict__ ktab, const double* __restrict__ a,
                                                        const double* __restrict__ c, double* __restrict__ s,
                                                        SrcPrep* __restrict__ prep, double* __restrict__ ds,
                                                        double* __restrict__ qsrc, int32_t* __restrict__ sdef,
                                                        double* __restrict__ svar, const int32_t* __restrict__ order,
                                                        double* __restrict__ rhs) {
     constexpr int GPB = 256 / G;
-    __shared__ double pool[GPB][23];
-    __shared__ __align__(16) char stage[4][STAGE_BYTES];
     const int gl = threadIdx.x % G;
     // group k takes the k-th source of the launch order
-    const int64_t kb = (int64_t)blockIdx.x * GPB;
-    const int64_t kg = kb + threadIdx.x / G;
+    const int64_t kg = (int64_t)blockIdx.x * GPB + threadIdx.x / G;
     const bool valid = kg < n_src;
-    SourceDir sd;
+    const int64_t i = valid ? order[kg] : 0;
+    double alpha = 0.0, delta = 0.0, plx = 0.0, pma = 0.0, pmd = 0.0;
     int64_t l0 = 0, l1 = 0;
-    double cd;
-    ObsStream<SigT> st{ot, oeta, osig, ocell, oell, a, knots, ktab, c, nullptr, stage[threadIdx.x >> 6]};
-    int trips, mine;                     // the wavefront's and this lane's records
-    {
-        double alpha = 0.0, delta = 0.0, plx = 0.0, pma = 0.0, pmd = 0.0;
-        if (valid) {
-            const int64_t i = order[kg];
-            l0 = off[i];
-            l1 = off[i + 1];
-            const double* si = s + 5 * i;
-            alpha = si[0];
-            delta = si[1];
-            plx = si[2];
-            pma = si[3];
-            pmd = si[4];
-        }
-        trips = wave_trips<G>(l0, l1);
-        mine = (int)(l1 - l0 - gl + G - 1) / G;
-        if (trips > 0) st.start(l0 + gl, l1, G);
-        cd = source_dir(k, alpha, delta, plx, pma, pmd, sd);
-        if (trips > 0) st.gather(k, 0);
+    if (valid) {
+        const double* si = s + 5 * i;
+        alpha = si[0];
+        delta = si[1];
+        plx = si[2];
+        pma = si[3];
+        pmd = si[4];
+        l0 = off[i];
+        l1 = off[i + 1];
     }
+    double sa, ca, sd, cd;
+    sincos(alpha, &sa, &ca);
+    sincos(delta, &sd, &cd);
+    const double p[3] = {-sa, ca, 0.0};
+    const double q[3] = {-sd * ca, -sd * sa, cd};
+    const double r[3] = {cd * ca, cd * sa, sd};
+    double mu[3];
+#pragma unroll
+    for (int cc = 0; cc < 3; ++cc) mu[cc] = p[cc] * pma + q[cc] * pmd;
+
     double acc[21];
 #pragma unroll
     for (int e = 0; e < 21; ++e) acc[e] = 0.0;
@@ -104,16 +100,50 @@ __global__ __launch_bounds__(256, 2) void k_source_update(DevConsts k, int64_t n
     float fs[MIXED ? 15 : 1], fc[MIXED ? 15 : 1];
 #pragma unroll
     for (int e = 0; e < (MIXED ? 15 : 1); ++e) fs[e] = fc[e] = 0.0f;
-    auto record = [&](int u, int at) {
-        double qa[4], sL, cL;
-        st.take(k, u, qa, sL, cL);
-        const double t = st.t[u], obs = st.e[u] + st.cal;
-        const bool ac = AC && st.cf[u] >= k.ac_cf0;
-        const double sg = (double)st.s[u];
-        st.advance(k, u);
-        if (at >= mine) return;
-        double A[5], R, tau;
-        source_row<AC, DEFL>(k, sd, qa, sL, cL, t - k.t_ep, obs, ac, A, R, tau);
+    int64_t l = l0 + gl;
+    // Current observation: columns, and the gathered attitude coefficients,
+    // interval table entry and calibration of its cell.  The next
+    // observation's columns load at the top of an iteration, its gathers
+    // after the current observation has been evaluated.
+    double t_c = 0.0, e_c = 0.0, cal_c = 0.0;
+    SigT s_c = 1;
+    int32_t ell_c = 3;
+    bool ac_c = false;
+    double a_c[16];
+    KnotTab kt_c = {0.0, 1.0, 0.0, 0.0};
+#pragma unroll
+    for (int e = 0; e < 16; ++e) a_c[e] = 0.0;
+    if (l < l1) {
+        t_c = ot[l];
+        e_c = oeta[l];
+        s_c = osig[l];
+        ell_c = oell[l];
+        const int32_t cf = ocell[l];
+        cal_c = c[cf >> 1];
+        ac_c = AC && cf >= k.ac_cf0;
+        const double* a4 = a + 4 * (ell_c - 3);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) a_c[e] = a4[e];
+        kt_c = ktab[ell_c - 3];
+    }
+    for (; l < l1; l += G) {
+        const int64_t ln = l + G;
+        const bool more = ln < l1;
+        double t_n = 0.0, e_n = 0.0;
+        SigT s_n = 1;
+        int32_t c_n = 0, ell_n = 3;
+        if (more) {
+            t_n = ot[ln];
+            e_n = oeta[ln];
+            s_n = osig[ln];
+            c_n = ocell[ln];
+            ell_n = oell[ln];
+        }
+        ObsEval o;
+        observe<DEFL>(k, t_c, e_c, cal_c, r, mu, plx, a_c, knots + (ell_c - 2), kt_c, o, ac_c);
+        double A[5];
+        source_partials(o, p, q, r, A, ac_c);
+        const double sg = (double)s_c;
         const double W = rcp_nr(sg * sg);
         if constexpr (MIXED) {
             float Af[5];
@@ -130,24 +160,32 @@ __global__ __launch_bounds__(256, 2) void k_source_update(DevConsts k, int64_t n
                     ++e;
                 }
             }
-        }
-        int e = 0;
 #pragma unroll
-        for (int rr = 0; rr < 5; ++rr) {
-            const double wa = W * A[rr];
-            if constexpr (!MIXED) {
+            for (int rr = 0; rr < 5; ++rr) acc[15 + rr] += W * A[rr] * o.R;
+            acc[20] += W * o.R * o.R;
+        } else {
+            int e = 0;
+#pragma unroll
+            for (int rr = 0; rr < 5; ++rr) {
+                const double wa = W * A[rr];
 #pragma unroll
                 for (int cc = rr; cc < 5; ++cc) acc[e++] += wa * A[cc];
             }
-            acc[15 + rr] += wa * R;
-        }
-        acc[20] += W * R * R;
-    };
-    for (int it = 0; it < trips; it += OBS_AHEAD) {
 #pragma unroll
-        for (int u = 0; u < OBS_AHEAD; ++u) {
-            if (it + u >= trips) break;
-            record(u, it + u);
+            for (int rr = 0; rr < 5; ++rr) acc[15 + rr] += W * A[rr] * o.R;
+            acc[20] += W * o.R * o.R;
+        }
+        t_c = t_n;
+        e_c = e_n;
+        s_c = s_n;
+        ell_c = ell_n;
+        if (more) {
+            cal_c = c[c_n >> 1];
+            ac_c = AC && c_n >= k.ac_cf0;
+            const double* a4 = a + 4 * (ell_n - 3);
+#pragma unroll
+            for (int e2 = 0; e2 < 16; ++e2) a_c[e2] = a4[e2];
+            kt_c = ktab[ell_n - 3];
         }
     }
     if constexpr (MIXED) {
@@ -156,33 +194,30 @@ __global__ __launch_bounds__(256, 2) void k_source_update(DevConsts k, int64_t n
     }
 #pragma unroll
     for (int e = 0; e < 21; ++e) acc[e] = group_sum<G>(acc[e]);
-    // the block's sources finish in the first lanes of its first wavefront: by
-    // the group leaders, one lane in G, every wavefront would run the solves
-    // (with division-free solves: 20,000 sources 44 -> 27 us, 1M sources of
-    // 223 records 4.25 -> 3.83 ms)
-    if (gl == 0) {
-#pragma unroll
-        for (int e = 0; e < 21; ++e) pool[threadIdx.x / G][e] = acc[e];
-        pool[threadIdx.x / G][21] = cd;
-    }
-    __syncthreads();
-    if (threadIdx.x >= GPB) return;
-    const int64_t kf = kb + threadIdx.x;
-    if (kf >= n_src) return;
-    const int64_t fi = order[kf];
-    double sum[21];
-#pragma unroll
-    for (int e = 0; e < 21; ++e) sum[e] = pool[threadIdx.x][e];
-    const double* si = s + 5 * fi;
-    source_finish(sum, fi, si[0], si[1], si[2], si[3], si[4], pool[threadIdx.x][21], s, prep, ds, qsrc, sdef, svar, rhs);
+    if (!valid || gl != 0) return;
+    source_finish(acc, i, alpha, delta, plx, pma, pmd, cd, s, prep, ds, qsrc, sdef, svar, rhs);
 }
 
 // ------------------------------------------------------------- A/C pass
 typedef double double4_t __attribute__((ext_vector_type(4)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
-constexpr int AC_WAVES = 1;             // wavefronts per block, one knot interval each (2 and 4 measured 4% and 7% slower)
-constexpr int AC_XS = 33;               // LDS row stride (doubles) of the transposition buffer
+// A row of the transposition buffer.  FP64: B_0..B_3, 1, [fov +1], [fov -1],
+// then b; the reading lanes form a's products, so that three wavefronts' buffers
+// per SIMD fit a compute unit's LDS.  Mixed precision: a, then b.  (Odd strides:
+// no bank conflicts.)
+constexpr int AC_ROW = 25, AC_B = 7;
+constexpr int AC_ROW_MIXED = 33;
+
+// The A/C pass's gathers, one chunk of 64 records ahead.
+struct AcRecord {
+    double t, e, cal, ea;
+    int32_t cf;
+    int iv;                                // knot interval within the wavefront's range
+    int32_t pos;                           // place in the geometric calibration's group order, or -1
+    bool mine;                             // the lane's slot holds an observation
+    SrcPrep sp;
+};
 
 // A/C accumulation as a matrix product on the FP64 matrix cores.  Every
 // observation of knot interval j gives two 16-vectors
@@ -191,9 +226,21 @@ constexpr int AC_XS = 33;               // LDS row stride (doubles) of the trans
 //        -W (g R - 2 lambda^2 q D) (4), W, W R)
 // and the interval's sums are blocks of C = sum over observations of a b'
 // (16 x 16): pairs x entries (eq:normAmod), B_n x right-hand side, and
-// fov x (W, W R) for eq:normC.  One wavefront takes 64 observations at a
-// time (one per lane), writes (a, b) to LDS and feeds them to 16
-// v_mfma_f64_16x16x4 steps, four observations each.
+// fov x (W, W R) for eq:normC.  One wavefront takes RANGE neighbouring knot
+// intervals, 64 observations at a time (one per lane), writes b and the factors
+// of a to LDS and feeds them to v_mfma_f64_16x16x4 steps of four observations
+// of one interval each.
+//
+// An interval has 15 to 300 observations: one interval per wavefront leaves 29%
+// to 88% of the lanes' slots filled and starts the loads anew each time; over
+// eight they follow on (97%; 4 and 16 intervals: 4% and 2% slower).  A SIMD's
+// FP64 products and FP64 arithmetic share a pipe within a wavefront but not
+// between them, and no unit is busy for more than half of the time: latencies
+// bound it, at three wavefronts per SIMD (168 registers, 13 KB).  1M sources,
+// 223M observations: 7.04 -> 5.29 ms (27 bytes of columns and, by source, a
+// seventh of a 64-byte record per observation; two wavefronts 5.9; the next
+// columns asked for before the rows are written 5.37; 12 of 16 blocks by
+// v_mfma_f64_4x4x4, whose operands take two more reads, 5.49).
 //
 // Mixed precision (MIXED): the model stays FP64; a and b are formed in FP32
 // from single-precision partials, each 64-observation chunk is summed by
@@ -201,44 +248,65 @@ constexpr int AC_XS = 33;               // LDS row stride (doubles) of the trans
 // running sums, converted to FP64 for the band solve.
 // AC: across-scan observations present (cell/fov code from k.ac_cf0 on):
 // their rows carry the AC attitude partials and no calibration entries.
-template <bool MIXED, bool AC, typename SigT, bool DEFL = false>
-__global__ __launch_bounds__(64 * AC_WAVES) void k_ac_pass(DevConsts k, int64_t K, const int64_t* __restrict__ iv_off,
-                                                           const double* __restrict__ ot,
-                                                           const double* __restrict__ oeta,
-                                                           const SigT* __restrict__ osig,
-                                                           const int32_t* __restrict__ ocellfov,
-                                                           const int32_t* __restrict__ osrc,
-                                                           const SrcPrep* __restrict__ prep,
-                                                           const double* __restrict__ knots,
-                                                           const KnotTab* __restrict__ ktab,
-                                                           const double* __restrict__ a,
-                                                           const double* __restrict__ c,
-                                                           const double* __restrict__ eps_a2, int eps_bucket,
-                                                           int robust, double* __restrict__ iv_sums,
-                                                           double* __restrict__ iv_cal, double* __restrict__ wr_out,
-                                                           const int32_t* __restrict__ wr_pos) {
+template <bool MIXED, bool AC, typename SigT, bool DEFL, bool ROBUST, int RANGE>
+__global__ __launch_bounds__(64, MIXED ? 2 : 3) void k_ac_pass(DevConsts k, int64_t K, const int64_t* __restrict__ iv_off,
+                                                   const double* __restrict__ ot, const double* __restrict__ oeta,
+                                                   const SigT* __restrict__ osig,
+                                                   const int32_t* __restrict__ ocellfov,
+                                                   const int32_t* __restrict__ osrc,
+                                                   const SrcPrep* __restrict__ prep,
+                                                   const double* __restrict__ knots,
+                                                   const KnotTab* __restrict__ ktab, const double* __restrict__ a,
+                                                   const double* __restrict__ c, const double* __restrict__ eps_a2,
+                                                   int robust, double* __restrict__ iv_sums,
+                                                   double* __restrict__ iv_cal, double* __restrict__ wr_out,
+                                                   const int32_t* __restrict__ wr_pos) {
+    static_assert(!MIXED || RANGE == 1, "the FP64 sums of mixed precision belong to one interval");
     using XT = typename std::conditional<MIXED, float, double>::type;
-    __shared__ XT xb[AC_WAVES][64][AC_XS];
-    __shared__ double sh_a[AC_WAVES][16];
-    __shared__ double sh_k[AC_WAVES][6];
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    const int64_t j = (int64_t)blockIdx.x * AC_WAVES + wv;
-    const bool valid = j < K;
-    if (lane < 22) {
-        double v = 0.0;
-        if (valid) v = lane < 16 ? a[4 * j + lane] : knots[j + 1 + (lane - 16)];
-        if (lane < 16) sh_a[wv][lane] = v;
-        else sh_k[wv][lane - 16] = v;
+    constexpr int ROW = MIXED ? AC_ROW_MIXED : AC_ROW;
+    __shared__ __align__(16) XT xw[64][ROW];
+    __shared__ __align__(16) double sh_a[4 * (RANGE + 3)];
+    __shared__ __align__(16) double sh_k[4 * RANGE];
+    const int lane = threadIdx.x;
+    const int64_t j0 = (int64_t)blockIdx.x * RANGE;
+    const int count = (int)(K - j0 < RANGE ? K - j0 : RANGE);
+    const int64_t first = iv_off[j0];
+    // Slots for the range's observations, each interval's from a multiple of
+    // four on: no step of four observations spans two intervals.  Lane i holds
+    // the end of interval i's slots, what turns its slots into observations
+    // counted from the range's first, and the end of these.
+    int ends = 0, shift, stop;
+    {
+        const int64_t jl = j0 + (lane < count ? lane : count - 1);
+        const int start = (int)(iv_off[jl] - first);
+        stop = (int)(iv_off[jl + 1] - first);
+        const int slots = lane < count ? (stop - start + 3) & ~3 : 0;
+        ends = slots;
+#pragma unroll
+        for (int m = 1; m < RANGE; m <<= 1) {
+            const int below = __shfl_up(ends, m, 64);
+            ends += lane >= m ? below : 0;
+        }
+        shift = start - (ends - slots);
     }
-    __syncthreads();
-    const double lam2 = k.lam2;
-    const int64_t l0 = valid ? iv_off[j] : 0, l1 = valid ? iv_off[j + 1] : 0;
-    const KnotTab kt = valid ? ktab[j] : KnotTab{0.0, 1.0, 0.0, 0.0};
-    // robust: sigma~^2 = sigma^2 + eps_a^2 of the record's component in the
-    // interval's bucket (eq:W)
-    XT (*xw)[AC_XS] = xb[wv];
+    if (lane < 4 * (count + 3)) sh_a[lane] = a[4 * j0 + lane];
+    if (lane < 4 * count) sh_k[lane] = reinterpret_cast<const double*>(ktab + j0)[lane];
+    const int n = __builtin_amdgcn_readlane(ends, RANGE - 1);
+    const double lam2x4 = 4.0 * k.lam2;
     const int ri = lane & 15, rk = lane >> 4;
+    // this lane's operands of step kk, 4 kk rows on (FP64: a is a product of two
+    // entries)
+    const XT *at, *at2 = nullptr, *atb;
+    if constexpr (MIXED) {
+        at = &xw[rk][ri];
+        atb = &xw[rk][16 + ri];
+    } else {
+        const int f1 = ri < 4 ? 0 : ri < 7 ? 1 : ri < 9 ? 2 : ri < 10 ? 3 : ri < 14 ? ri - 10 : ri - 9;
+        const int f2 = ri < 4 ? ri : ri < 7 ? ri - 3 : ri < 9 ? ri - 5 : ri < 10 ? 3 : 4;
+        at = &xw[rk][f1];
+        at2 = &xw[rk][f2];
+        atb = &xw[rk][AC_B + ri];
+    }
     double4_t C = {0.0, 0.0, 0.0, 0.0};
     float4_t Cs = {0.0f, 0.0f, 0.0f, 0.0f}, Cc = {0.0f, 0.0f, 0.0f, 0.0f};
     // mixed precision: the right-hand sides (B_n times the 4 attitude
@@ -250,141 +318,226 @@ __global__ __launch_bounds__(64 * AC_WAVES) void k_ac_pass(DevConsts k, int64_t 
     for (int e = 0; e < (MIXED ? 16 : 1); ++e) rb[e] = 0.0;
 #pragma unroll
     for (int e = 0; e < (MIXED ? 4 : 1); ++e) cb[e] = 0.0;
-    // lanes past the end evaluate the interval's last observation again with
-    // weight zero
-    int64_t base = l0;
-    double t_c = 0.0, e_c = 0.0;
-    SigT s_c = 1;
-    int32_t cf_c = 0;
-    bool h_c = false;
-    SrcPrep sp_c = {};
-    if (base < l1) {
-        h_c = base + lane < l1;
-        const int64_t le = h_c ? base + lane : l1 - 1;
-        t_c = ot[le];
-        e_c = oeta[le];
-        s_c = osig[le];
-        cf_c = ocellfov[le];
-        sp_c = prep[osrc[le]];
-    }
-    for (; base < l1; base += 64) {
-        const int64_t bn = base + 64;
-        double t_n = 0.0, e_n = 0.0;
-        SigT s_n = 1;
-        int32_t cf_n = 0, src_n = 0;
-        bool h_n = false;
-        if (bn < l1) {
-            h_n = bn + lane < l1;
-            const int64_t le = h_n ? bn + lane : l1 - 1;
-            t_n = ot[le];
-            e_n = oeta[le];
-            s_n = osig[le];
-            cf_n = ocellfov[le];
-            src_n = osrc[le];
-        }
-        {
-            const bool ac = AC && cf_c >= k.ac_cf0;
-            ObsEval o;
-            observe<DEFL>(k, t_c, e_c, c[cf_c >> 1], sp_c.r, sp_c.mu, sp_c.plx, sh_a[wv], sh_k[wv], kt, o, ac);
-            double g[4];
-            attitude_partial(o, g, ac);
-            const double sg = (double)s_c;
-            double W;
-            if (robust) {
-                // robust mode 2: plus the source's excess noise eps_i^2 (eq:W)
-                const double s2 = sg * sg + eps_a2[eps_slot(k, cf_c, j)] + (robust == 2 ? sp_c.pad : 0.0);
-                W = h_c ? down_weight(o.R / sqrt(s2)) / s2 : 0.0;
-            } else {
-                W = h_c ? rcp_nr(sg * sg) : 0.0;
-            }
-            // geometric calibration: each along-scan record's W and W R for
-            // its C block, at its place in the group order
-            if (wr_out && h_c) {
-                const int32_t p = wr_pos[base + lane];
-                if (p >= 0) {
-                    wr_out[2 * (int64_t)p] = W;
-                    wr_out[2 * (int64_t)p + 1] = W * o.R;
-                }
-            }
-            XT* row = xw[lane];
-            const int f = cf_c & 1;
-            if constexpr (MIXED) {
-                float B[4], gf[4], qf[4];
-#pragma unroll
-                for (int n = 0; n < 4; ++n) {
-                    B[n] = (float)o.B[n];
-                    gf[n] = (float)g[n];
-                    qf[n] = (float)o.qraw[n];
-                }
-                const float Wf = (float)W, Rf = (float)o.R, Df = (float)o.D, l2 = (float)lam2;
-                int e = 0;
-#pragma unroll
-                for (int n = 0; n < 4; ++n)
-#pragma unroll
-                    for (int m = n; m < 4; ++m) row[e++] = B[n] * B[m];
-#pragma unroll
-                for (int n = 0; n < 4; ++n) row[10 + n] = B[n];
-                row[14] = (f == 0 && !ac) ? 1.0f : 0.0f;
-                row[15] = (f == 1 && !ac) ? 1.0f : 0.0f;
-                e = 0;
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr)
-#pragma unroll
-                    for (int cc = rr; cc < 4; ++cc) row[16 + e++] = Wf * (gf[rr] * gf[cc] + 4.0f * l2 * qf[rr] * qf[cc]);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) row[26 + rr] = -Wf * (gf[rr] * Rf - 2.0f * l2 * qf[rr] * Df);
-                row[30] = Wf;
-                row[31] = Wf * Rf;
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const double rhs = -W * (g[rr] * o.R - 2.0 * lam2 * o.qraw[rr] * o.D);
-#pragma unroll
-                    for (int n = 0; n < 4; ++n) rb[4 * n + rr] += o.B[n] * rhs;
-                }
-                if (!ac) {
-                    cb[2 * f] += W;
-                    cb[2 * f + 1] += W * o.R;
-                }
-            } else {
-                int e = 0;
-#pragma unroll
-                for (int n = 0; n < 4; ++n)
-#pragma unroll
-                    for (int m = n; m < 4; ++m) row[e++] = o.B[n] * o.B[m];
-#pragma unroll
-                for (int n = 0; n < 4; ++n) row[10 + n] = o.B[n];
-                row[14] = (f == 0 && !ac) ? 1.0 : 0.0;
-                row[15] = (f == 1 && !ac) ? 1.0 : 0.0;
-                e = 0;
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr)
-#pragma unroll
-                    for (int cc = rr; cc < 4; ++cc)
-                        row[16 + e++] = W * (g[rr] * g[cc] + 4.0 * lam2 * o.qraw[rr] * o.qraw[cc]);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) row[26 + rr] = -W * (g[rr] * o.R - 2.0 * lam2 * o.qraw[rr] * o.D);
-                row[30] = W;
-                row[31] = W * o.R;
-            }
-        }
-        SrcPrep sp_n = {};
-        if (bn < l1) sp_n = prep[src_n];
-        // the rows just written are read back below by other lanes: a
-        // workgroup barrier (the block is one wavefront, so it reduces to
-        // waiting for the LDS stores) orders the stores before the reads
-        __syncthreads();
-        // groups of four observations past the interval's end hold padding
-        // rows of weight zero: their matrix-core steps would add zeros
-        const int64_t n_here = l1 - base < 64 ? l1 - base : 64;
-        const int steps = (int)((n_here + 3) >> 2);
+
+    // Where this lane's sums of the first interval go, and how far the next
+    // one's are.  Lane l holds C[4 v + l / 16][l % 16] (FP64 product) or
+    // C[4 (l / 16) + v][l % 16] (FP32 product), v = 0..3.  FP64: v = 0, 1 are
+    // pairs, the lower half of v = 2 too, the upper half and the lower one of v
+    // = 3 right-hand sides, the rest calibration sums.
+    double* out = iv_sums + j0 * IV_SUMS + rk * 10 + ri;
+    double* out2 = iv_sums + j0 * IV_SUMS + (rk < 2 ? 80 + rk * 10 + ri : 92 + (rk - 2) * 4 + (ri - 2));
+    double* out3 = rk < 2 ? iv_sums + j0 * IV_SUMS + 98 + rk * 4 + ri
+                          : iv_cal + j0 * IV_CAL + (rk - 2) * 2 + (ri - 14);
+    const int step3 = rk < 2 ? IV_SUMS : IV_CAL;
+    const bool mid = ri >= 10 && ri < 14;
+    const bool has2 = rk < 2 ? ri < 10 : mid, has3 = rk < 2 ? mid : ri >= 14;
+    // the sums of interval `now` go out
+    int now = 0;
+    auto flush = [&]() {
         if constexpr (MIXED) {
+            const int64_t j = j0 + now;
+            double* to = iv_sums + j * IV_SUMS;
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) rb[e] += __shfl_xor(rb[e], m, 64);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) cb[e] += __shfl_xor(cb[e], m, 64);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = 4 * rk + v;
+                if (i < 10 && ri < 10) to[i * 10 + ri] = (double)Cs[v] - (double)Cc[v];
+            }
+            // every lane holds the reduced FP64 sums; lane e writes entry e
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (lane == e) to[100 + e] = rb[e];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (lane == 16 + e) iv_cal[j * IV_CAL + e] = cb[e];
+        } else {
+            if (ri < 10) {
+                out[0] = C[0];
+                out[40] = C[1];
+            }
+            if (has2) *out2 = C[2];
+            if (has3) *out3 = C[3];
+            out += IV_SUMS;
+            out2 += IV_SUMS;
+            out3 += step3;
+            C = double4_t{0.0, 0.0, 0.0, 0.0};
+        }
+        ++now;
+    };
+
+    // columns two chunks ahead, gathers one; a slot without an observation
+    // takes its interval's last again, with weight zero
+    double t_n = 0.0, e_n = 0.0;
+    SigT s_n = 1, s_g = 1;
+    int32_t cf_n = 0, src_n = 0, pos_n = -1, iv_n = 0;
+    bool mine_n = false;
+    AcRecord g = {};
+    int iv_load = 0;                       // interval of the first slot to load
+    auto load = [&](int base) {
+        const int slot = base + lane < n ? base + lane : n - 1;
+        iv_n = iv_load;
+        int by = __builtin_amdgcn_readlane(shift, iv_load), past = __builtin_amdgcn_readlane(stop, iv_load);
+        while (iv_load + 1 < count) {
+            const int end = __builtin_amdgcn_readlane(ends, iv_load);
+            if (end > base + 64) break;
+            ++iv_load;
+            const bool on = slot >= end;
+            iv_n = on ? iv_load : iv_n;
+            by = on ? __builtin_amdgcn_readlane(shift, iv_load) : by;
+            past = on ? __builtin_amdgcn_readlane(stop, iv_load) : past;
+        }
+        const int at = slot + by;
+        mine_n = at < past && base + lane < n;
+        // from a base that the wavefront shares: a slot is at most 3 RANGE
+        // further on than its observation
+        constexpr int BACK = 4 * RANGE;
+        const int64_t from = first + base - BACK;
+        const uint32_t l = (uint32_t)((at < past ? at : past - 1) - (base - BACK));
+        auto column = [&](auto* p) {
+            return *reinterpret_cast<decltype(p)>(reinterpret_cast<const char*>(p + from) + (uint32_t)(l * sizeof(*p)));
+        };
+        t_n = column(ot);
+        e_n = column(oeta);
+        s_n = column(osig);
+        cf_n = column(ocellfov);
+        src_n = column(osrc);
+        if (wr_out) pos_n = column(wr_pos);
+    };
+    auto gather = [&]() {
+        g.t = t_n;
+        g.e = e_n;
+        g.cf = cf_n;
+        g.pos = mine_n ? pos_n : -1;
+        g.iv = iv_n;
+        g.mine = mine_n;
+        s_g = s_n;
+        g.sp = prep[src_n];
+        g.cal = c[cf_n >> 1];
+        if constexpr (ROBUST) g.ea = eps_a2[eps_slot(k, cf_n, j0 + iv_n)];
+    };
+    __syncthreads();
+    if (n > 0) {
+        load(0);
+        gather();
+        if (n > 64) load(64);
+    }
+    for (int base = 0; base < n; base += 64) {
+        const bool ac = AC && g.cf >= k.ac_cf0;
+        TimeRow o;
+        {
+            double p[16];
+            const double2_t* own = reinterpret_cast<const double2_t*>(sh_a + 4 * g.iv);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const double2_t v = own[i];
+                p[2 * i] = v.x;
+                p[2 * i + 1] = v.y;
+            }
+            const double2_t* own_k = reinterpret_cast<const double2_t*>(sh_k + 4 * g.iv);
+            const double2_t k0 = own_k[0], k1 = own_k[1];
+            const KnotTab kt = {k0.x, k0.y, k1.x, k1.y};
+            time_row<AC, DEFL>(k, g.sp, p, kt, knots + (j0 + g.iv + 1), g.t, g.e + g.cal, ac, o);
+        }
+        const double sg = (double)s_g;
+        double W;
+        if constexpr (ROBUST) {
+            // sigma~^2 = sigma^2 + eps_a^2 of the record's component in the
+            // interval's bucket; robust mode 2: plus the source's excess noise
+            // eps_i^2 (eq:W)
+            const double s2 = sg * sg + g.ea + (robust == 2 ? g.sp.pad : 0.0);
+            W = down_weight(o.R * rsqrt_nr(s2)) * rcp_nr(s2);
+        } else {
+            W = rcp_nr(sg * sg);
+        }
+        W = g.mine ? W : 0.0;
+        // geometric calibration: each along-scan record's W and W R for its C
+        // block, at its place in the group order
+        if (g.pos >= 0) reinterpret_cast<double2_t*>(wr_out)[g.pos] = double2_t{W, W * o.R};
+        const int f = g.cf & 1;
+        // the next chunk's gathers, and the columns of the one after it
+        if (base + 64 < n) {
+            gather();
+        }
+        XT* row = xw[lane];
+        if constexpr (MIXED) {
+            float B[4], gf[4], qf[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                B[m] = (float)o.B[m];
+                gf[m] = (float)o.g[m];
+                qf[m] = (float)o.q[m];
+            }
+            const float Wf = (float)W, Rf = (float)o.R, Df = (float)o.D, l2 = (float)k.lam2;
+            int e = 0;
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+#pragma unroll
+                for (int mm = m; mm < 4; ++mm) row[e++] = B[m] * B[mm];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) row[e++] = B[m];
+            row[e++] = (f == 0 && !ac) ? 1.0f : 0.0f;
+            row[e++] = (f == 1 && !ac) ? 1.0f : 0.0f;
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+                for (int cc = rr; cc < 4; ++cc) row[e++] = Wf * (gf[rr] * gf[cc] + 4.0f * l2 * qf[rr] * qf[cc]);
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) row[e++] = -Wf * (gf[rr] * Rf - 2.0f * l2 * qf[rr] * Df);
+            row[e++] = Wf;
+            row[e] = Wf * Rf;
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) {
+                const double rhs = -W * (o.g[rr] * o.R - 0.5 * lam2x4 * o.q[rr] * o.D);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) rb[4 * m + rr] += o.B[m] * rhs;
+            }
+            if (!ac) {
+                cb[2 * f] += W;
+                cb[2 * f + 1] += W * o.R;
+            }
+        } else {
+#pragma unroll
+            for (int m = 0; m < 4; ++m) row[m] = o.B[m];
+            row[4] = 1.0;
+            row[5] = (f == 0 && !ac) ? 1.0 : 0.0;
+            row[6] = (f == 1 && !ac) ? 1.0 : 0.0;
+            double wg[4], wq[4];
+            const double wl = W * lam2x4;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                wg[m] = W * o.g[m];
+                wq[m] = wl * o.q[m];
+            }
+            XT* b = row + AC_B;
+            int e = 0;
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+                for (int cc = rr; cc < 4; ++cc) b[e++] = wg[rr] * o.g[cc] + wq[rr] * o.q[cc];
+            const double hd = 0.5 * o.D;
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr) b[10 + rr] = wq[rr] * hd - wg[rr] * o.R;
+            b[14] = W;
+            b[15] = W * o.R;
+        }
+        wave_fence();
+        if constexpr (MIXED) {
+            if (base + 128 < n) load(base + 128);
+            // groups of four observations past the interval's end hold padding
+            // rows of weight zero: their matrix-core steps would add zeros
+            const int steps = n - base < 64 ? (n - base + 3) >> 2 : 16;
             float4_t Ck = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int kk = 0; kk < 16; ++kk) {
                 if (kk >= steps) break;
-                const float av = xw[4 * kk + rk][ri];
-                const float bv = xw[4 * kk + rk][16 + ri];
-                Ck = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, Ck, 0, 0, 0);
+                const int d = 4 * kk * ROW;
+                Ck = __builtin_amdgcn_mfma_f32_16x16x4f32(at[d], atb[d], Ck, 0, 0, 0);
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -394,55 +547,52 @@ __global__ __launch_bounds__(64 * AC_WAVES) void k_ac_pass(DevConsts k, int64_t 
                 Cc[v] = cv;
             }
         } else {
+            // operands of four steps in registers while the next four load (their
+            // latency, up to 300 clocks, is longer than a step's product, 64)
+            double av[4], zv[4], bv[4], an[4], zn[4], bn[4];
+            int end = __builtin_amdgcn_readlane(ends, now) - base;
+            auto fetch = [&](int q, double x[4], double z[4], double y[4]) {
 #pragma unroll
-            for (int kk = 0; kk < 16; ++kk) {
-                if (kk >= steps) break;
-                const double av = xw[4 * kk + rk][ri];
-                const double bv = xw[4 * kk + rk][16 + ri];
-                C = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, C, 0, 0, 0);
+                for (int u = 0; u < 4; ++u) {
+                    x[u] = at[(16 * q + 4 * u) * ROW];
+                    z[u] = at2[(16 * q + 4 * u) * ROW];
+                    y[u] = atb[(16 * q + 4 * u) * ROW];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto steps = [&](int row, double x[4], const double z[4], const double y[4]) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] *= z[u];
+                if (end - row >= 16) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) C = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u], y[u], C, 0, 0, 0);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        // the interval's sums are complete (and empty ones')
+                        while (row + 4 * u >= end && now + 1 < count) {
+                            flush();
+                            end = __builtin_amdgcn_readlane(ends, now) - base;
+                        }
+                        if (row + 4 * u < end) C = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u], y[u], C, 0, 0, 0);
+                    }
+                }
+            };
+            fetch(0, av, zv, bv);
+            if (base + 128 < n) load(base + 128);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll 1
+            for (int q = 0; q < 4; q += 2) {
+                fetch(q + 1, an, zn, bn);
+                steps(16 * q, av, zv, bv);
+                if (q < 2) fetch(q + 2, av, zv, bv);
+                steps(16 * q + 16, an, zn, bn);
             }
         }
-        // the next chunk's stores overwrite these rows: every lane's reads
-        // above come first
-        __syncthreads();
-        t_c = t_n;
-        e_c = e_n;
-        s_c = s_n;
-        cf_c = cf_n;
-        h_c = h_n;
-        sp_c = sp_n;
+        wave_fence();
     }
-    if (!valid) return;
-    if constexpr (MIXED) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) C[v] = (double)Cs[v] - (double)Cc[v];
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) rb[e] += __shfl_xor(rb[e], m, 64);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) cb[e] += __shfl_xor(cb[e], m, 64);
-        }
-    }
-    // lane l holds C[4 v + l / 16][l % 16] (FP64 product) or
-    // C[4 (l / 16) + v][l % 16] (FP32 product), v = 0..3
-    double* out = iv_sums + j * IV_SUMS;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int i = MIXED ? 4 * rk + v : 4 * v + rk, jj = ri;
-        if (i < 10 && jj < 10) out[i * 10 + jj] = C[v];
-        else if (!MIXED && i >= 10 && i < 14 && jj >= 10 && jj < 14) out[100 + (i - 10) * 4 + (jj - 10)] = C[v];
-        else if (!MIXED && i >= 14 && jj >= 14) iv_cal[j * IV_CAL + (i - 14) * 2 + (jj - 14)] = C[v];
-    }
-    if constexpr (MIXED) {
-        // every lane holds the reduced FP64 sums; lane e writes entry e
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-            if (lane == e) out[100 + e] = rb[e];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (lane == 16 + e) iv_cal[j * IV_CAL + e] = cb[e];
-    }
+    // the last interval, and the empty ones before and after the observations
+    while (now < count) flush();
 }
 
 // ------------------------------------------------------------ band solve
@@ -676,28 +826,44 @@ void launch_source_update(agis_ctx* ctx) {
     }
 }
 
-template <typename T>
+// Knot intervals per wavefront of the A/C pass.
+constexpr int AC_RANGE = 8;
+
+template <int RANGE, typename KERN, typename T>
+static void ac_launch(agis_ctx* ctx, KERN kern, const T* sig) {
+    kern<<<(unsigned)((ctx->K + RANGE - 1) / RANGE), 64, 0, ctx->stream>>>(
+        ctx->k, ctx->K, ctx->iv_off, ctx->t_t, ctx->t_eta, sig, ctx->t_cellfov, ctx->t_src, ctx->prep, ctx->knots,
+        ctx->ktab, ctx->a, ctx->c, ctx->eps_a2, robust_now(ctx), ctx->iv_sums, ctx->iv_cal,
+        ctx->geo_ccds > 0 ? ctx->geo_wr : nullptr, ctx->geo_pos);
+}
+
+template <bool ROBUST, typename T>
 static void ac_pass_with(agis_ctx* ctx, const T* sig) {
-    auto kern = ctx->cfg.precision == AGIS_MIXED
-                    ? (ctx->has_ac ? k_ac_pass<true, true, T> : k_ac_pass<true, false, T>)
-                    : (ctx->has_ac ? k_ac_pass<false, true, T> : k_ac_pass<false, false, T>);
+    if (ctx->cfg.precision == AGIS_MIXED) {
+        ac_launch<1>(ctx, ctx->has_ac ? k_ac_pass<true, true, T, false, ROBUST, 1>
+                                      : k_ac_pass<true, false, T, false, ROBUST, 1>, sig);
+        return;
+    }
+    auto kern = ctx->has_ac ? k_ac_pass<false, true, T, false, ROBUST, AC_RANGE>
+                            : k_ac_pass<false, false, T, false, ROBUST, AC_RANGE>;
     if constexpr (std::is_same<T, float>::value) {
         // the model with the Sun's light deflection (FP64 only, as the
         // global block requires)
-        if (ctx->k.defl > 0.0) kern = ctx->has_ac ? k_ac_pass<false, true, float, true> : k_ac_pass<false, false, float, true>;
+        if (ctx->k.defl > 0.0)
+            kern = ctx->has_ac ? k_ac_pass<false, true, T, true, ROBUST, AC_RANGE>
+                               : k_ac_pass<false, false, T, true, ROBUST, AC_RANGE>;
     }
-    kern<<<(unsigned)((ctx->K + AC_WAVES - 1) / AC_WAVES), 64 * AC_WAVES, 0, ctx->stream>>>(
-        ctx->k, ctx->K, ctx->iv_off, ctx->t_t, ctx->t_eta, sig, ctx->t_cellfov, ctx->t_src, ctx->prep, ctx->knots,
-        ctx->ktab, ctx->a, ctx->c, ctx->eps_a2, ctx->cfg.eps_bucket, robust_now(ctx), ctx->iv_sums, ctx->iv_cal,
-        ctx->geo_ccds > 0 ? ctx->geo_wr : nullptr, ctx->geo_pos);
+    ac_launch<AC_RANGE>(ctx, kern, sig);
 }
 
 void launch_ac_pass(agis_ctx* ctx) {
     if (ctx->K == 0) return;
     if (ctx->frozen)
-        ac_pass_with(ctx, ctx->t_sig_eff);
+        ac_pass_with<false>(ctx, ctx->t_sig_eff);
+    else if (robust_now(ctx))
+        ac_pass_with<true>(ctx, ctx->t_sig);
     else
-        ac_pass_with(ctx, ctx->t_sig);
+        ac_pass_with<false>(ctx, ctx->t_sig);
 }
 
 void launch_band_solve(agis_ctx* ctx) {

@@ -66,14 +66,21 @@ __device__ __forceinline__ double dot3(const double* a, const double* b) {
     return a[0] * b[0] + a[1] * b[1] + a[2] * b[2];
 }
 
-// 1/sqrt(x) to ~1 ulp: the hardware estimate (relative error 2^-24) and one
-// third-order step (at most 1.4e-16 over [2^-5, 2^5), measured; two Newton
-// steps took three instructions more and added their rounding last).
+// 1/sqrt(x) to ~1 ulp: hardware estimate and two Newton-Raphson steps.
+__device__ __forceinline__ double rsqrt_nr(double x) {
+    double y = __builtin_amdgcn_rsq(x);
+    y = y * (1.5 - 0.5 * x * y * y);
+    y = y * (1.5 - 0.5 * x * y * y);
+    return y;
+}
+
+// The hardware's estimate y of 1/sqrt(x) (relative error 2^-24) after one
+// third-order step: at most 1.4e-16 over [2^-5, 2^5), measured, and three
+// instructions less than two Newton-Raphson steps.
 __device__ __forceinline__ double rsqrt_refine(double x, double y) {
     const double e = __builtin_fma(-(x * y), y, 1.0);
     return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
 }
-__device__ __forceinline__ double rsqrt_nr(double x) { return rsqrt_refine(x, __builtin_amdgcn_rsq(x)); }
 
 // 1/sqrt(x) for x > 0, else 0 (Algorithm C1's rule for pivots).
 __device__ __forceinline__ double rsqrt_pivot(double x) {
@@ -81,12 +88,12 @@ __device__ __forceinline__ double rsqrt_pivot(double x) {
     return rsqrt_refine(x, x > 0.0 ? y : 0.0);
 }
 
-// 1/x to ~1 ulp: the hardware estimate (2^-24) and one third-order step (at
-// most 1.1e-16, measured).
+// 1/x to ~1 ulp: hardware estimate and two Newton-Raphson steps.
 __device__ __forceinline__ double rcp_nr(double x) {
-    const double y = __builtin_amdgcn_rcp(x);
-    const double e = __builtin_fma(-x, y, 1.0);
-    return __builtin_fma(y, __builtin_fma(e, e, e), y);
+    double y = __builtin_amdgcn_rcp(x);
+    y = y * (2.0 - x * y);
+    y = y * (2.0 - x * y);
+    return y;
 }
 
 // The four non-zero cubic B-splines B_{l-3..l}(t) on an arbitrary knot
@@ -99,18 +106,20 @@ __device__ __forceinline__ double rcp_nr(double x) {
 __device__ __forceinline__ void bspline4(const double* __restrict__ kn, double t, double B[4]) {
     // knot tau_{l+j} for j = -2..3
     auto tk = [&](int j) { return kn[j + 2]; };
+    // reciprocals of the orders' spans
+    const double i0 = rcp_nr(tk(1) - tk(0)), ia = rcp_nr(tk(1) - tk(-1)), ib = rcp_nr(tk(2) - tk(0));
+    const double ja = rcp_nr(tk(1) - tk(-2)), jb = rcp_nr(tk(2) - tk(-1)), jc = rcp_nr(tk(3) - tk(0));
     // order 2: B_{l-1}, B_l
-    const double h0 = tk(1) - tk(0);
-    const double b2m1 = (tk(1) - t) / h0, b20 = (t - tk(0)) / h0;
+    const double b2m1 = (tk(1) - t) * i0, b20 = (t - tk(0)) * i0;
     // order 3: B_{l-2}, B_{l-1}, B_l
-    const double b3m2 = (tk(1) - t) / (tk(1) - tk(-1)) * b2m1;
-    const double b3m1 = (t - tk(-1)) / (tk(1) - tk(-1)) * b2m1 + (tk(2) - t) / (tk(2) - tk(0)) * b20;
-    const double b30 = (t - tk(0)) / (tk(2) - tk(0)) * b20;
+    const double b3m2 = (tk(1) - t) * ia * b2m1;
+    const double b3m1 = (t - tk(-1)) * ia * b2m1 + (tk(2) - t) * ib * b20;
+    const double b30 = (t - tk(0)) * ib * b20;
     // order 4: B_{l-3} .. B_l
-    B[0] = (tk(1) - t) / (tk(1) - tk(-2)) * b3m2;
-    B[1] = (t - tk(-2)) / (tk(1) - tk(-2)) * b3m2 + (tk(2) - t) / (tk(2) - tk(-1)) * b3m1;
-    B[2] = (t - tk(-1)) / (tk(2) - tk(-1)) * b3m1 + (tk(3) - t) / (tk(3) - tk(0)) * b30;
-    B[3] = (t - tk(0)) / (tk(3) - tk(0)) * b30;
+    B[0] = (tk(1) - t) * ja * b3m2;
+    B[1] = (t - tk(-2)) * ja * b3m2 + (tk(2) - t) * jb * b3m1;
+    B[2] = (t - tk(-1)) * jb * b3m1 + (tk(3) - t) * jc * b30;
+    B[3] = (t - tk(0)) * jc * b30;
 }
 
 // Attitude matrix A = S'C of a unit quaternion (eq:quat2mat), row-major.
@@ -371,172 +380,162 @@ __device__ __forceinline__ void global_partials(const ObsEval& o, const double r
     a_g0 = (f * dot3(m, o.dudg) - mu_ * dot3(o.vc, o.dudg)) * secz;
 }
 
-// The library functions that observations in range never need, kept out of
-// line: inlined, their constants and temporaries cost the S pass a third of
-// its registers.
-__device__ __attribute__((noinline)) inline double far_angle(double y, double x) { return atan2(y, x); }
-__device__ __attribute__((noinline)) inline double2 far_orbit(double L) {
-    double2 o;
-    sincos(L, &o.x, &o.y);
-    return o;
+// atan2(y, x) to rounding in relative terms, without the library function's
+// registers (which cost the passes a third of theirs, inlined or called): the
+// half-angle formula until |tan| < 1e-2 (nine times from pi), an odd series,
+// and twice the angle as often.  inv_x: 1 / x of the halved angle's last pair.
+__device__ __forceinline__ double angle_of(double x, double y, double& inv_x, double& tan2, bool& near) {
+    double scale = 1.0;
+    near = x > 0.0 && fabs(y) < 1e-2 * x;
+    if (__builtin_expect(!near, 0)) {
+#pragma unroll 1
+        for (int m = 0; m < 12 && !(x > 0.0 && fabs(y) < 1e-2 * x); ++m) {
+            const double r2 = x * x + y * y, r = r2 * rsqrt_nr(r2), x0 = x;
+            x = x0 < 0.0 ? fabs(y) : r + x0;                        // x < 0: r + x cancels
+            y = x0 < 0.0 ? __builtin_copysign(r - x0, y) : y;
+            scale += scale;
+        }
+    }
+    inv_x = rcp_nr(x);
+    const double q = y * inv_x, q2 = q * q;
+    tan2 = q2;
+    return scale * (q + q * (q2 * (-1.0 / 3.0 + q2 * (1.0 / 5.0 + q2 * (-1.0 / 7.0 + q2 * (1.0 / 9.0))))));
 }
-
-// One source's data in the form source_row() takes: direction, proper-motion
-// vector, the triad's p (p_z = 0) and q, parallax times the orbit's radius.
-struct SourceDir {
-    double r[3], mu[3], p0, p1, q[3], plx_r;
-};
 
 __device__ __forceinline__ double copysign_of(double mag, double sgn) { return __builtin_copysign(mag, sgn); }
 
 // Sine and cosine of the observer's orbital longitude d past the interval's
-// start (Taylor series to d^6 for |d| < 1e-2, as in observe()).
-__device__ __forceinline__ void orbit_at(const DevConsts& k, const KnotTab& kt, double dt, double t, double& sL,
-                                         double& cL) {
-    const double d = k.eph_Lrate * dt;
-    if (__builtin_expect(fabs(d) < 1e-2, 1)) {
-        const double d2 = d * d;
-        const double sd = d * (1.0 - d2 * (1.0 / 6.0 - d2 * (1.0 / 120.0)));
-        const double cd = 1.0 - d2 * (0.5 - d2 * (1.0 / 24.0 - d2 * (1.0 / 720.0)));
-        sL = kt.sL * cd + kt.cL * sd;
-        cL = kt.cL * cd - kt.sL * sd;
-    } else {
-        const double2 o = far_orbit(k.eph_L0 + k.eph_Lrate * t);
-        sL = o.x;
-        cL = o.y;
+// start (Taylor series to d^6 for |d| < 1e-2, as in observe(); in a longer
+// interval of a fraction of d, doubled as often: its rounding, 2^n u, enters
+// through the aberration and the parallax, 1e-4 and less of it).
+__device__ __forceinline__ void orbit_at(const DevConsts& k, const KnotTab& kt, double dt, double& sL, double& cL) {
+    double d = k.eph_Lrate * dt;
+    int n = 0;
+    if (__builtin_expect(fabs(d) >= 1e-2, 0)) {
+#pragma unroll 1
+        for (; n < 64 && fabs(d) >= 1e-2; ++n) d *= 0.5;
     }
-}
-
-// Residual and design row -dR/ds of one observation for the S block: the
-// model of observe() and source_partials(), in a form that forms neither unit
-// vector nor unit quaternion.  qa: any multiple of the attitude quaternion
-// (sum a_n B_n as it is); sL, cL: the observer's orbital longitude; tt: t -
-// t_ep; obs: eta_obs (zeta_obs) plus the calibration.
-//  * The field angle needs the ratio of two components of M uu only (M =
-//    |q|^2 A, uu = ubar + v_G/c), for which lengths cancel: no third row of M
-//    along scan, no normalisation.
-//  * With S = M uu, m^ = M'(-S_y, S_x, 0) is |q|^2 rho_S times the AL unit
-//    vector m, and the design entry (f m.d - (m.ubar)(v.d)) sec zeta becomes
-//    (f m^.d - (m^.ubar)(v.d)) |uu| / rho_S^2; m is normal to uu, so m.ubar =
-//    -m.v (not with the deflection's term in uu); v.b = 0 on the circular
-//    orbit.  1/rho_S^2 comes from the reciprocal that the angle's quotient
-//    took (1 + z^2 in series for |z| < 1e-2).  Across scan M'(-S_x S_z, -S_y
-//    S_z, rho_S^2) is |q|^2 rho_S |S| n, and the factor |uu| / (rho_S |S|^2).
-// About 190 FP64 instructions along scan, 300 before; two reciprocal square
-// roots and one reciprocal.
-template <bool AC, bool DEFL>
-__device__ __forceinline__ void source_row(const DevConsts& k, const SourceDir& s, const double qa[4], double sL,
-                                           double cL, double tt, double obs, bool ac, double A[5], double& R,
-                                           double& tau) {
-    const double b[3] = {cL, k.cos_obl * sL, k.sin_obl * sL};          // in units of the orbit's radius
-    const double v[3] = {-k.vel * sL, k.vel_co * cL, k.vel_so * cL};
-    const double rb = dot3(s.r, b);
-    tau = (rb * k.au_r + tt) * k.inv_year;
-    double ub[3], uu[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) ub[c] = s.r[c] + tau * s.mu[c] - s.plx_r * b[c];
-    const double iub = rsqrt_nr(dot3(ub, ub));
-    const double bv = dot3(ub, v) * iub;
-    const double f = 1.0 - bv;
-    double uu2;
-    if constexpr (DEFL) {
-        // the Sun's light deflection, as in observe()
-        const double rad = k.eph_r;
-        const double ib = rsqrt_nr(rad * rad * dot3(b, b));
-        const double eu = dot3(b, ub) * (rad * ib * iub);
-        const double g = k.defl * ib / (1.0 + eu) * (2.0 + k.gpar[0]);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) uu[c] = ub[c] * iub + g * (b[c] * (rad * ib) - eu * ub[c] * iub) + v[c];
-        uu2 = dot3(uu, uu);
-    } else {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) uu[c] = ub[c] * iub + v[c];
-        uu2 = k.one_vel2 + 2.0 * bv;
-    }
-    const double nuu = uu2 * rsqrt_nr(uu2);
-    // |q|^2 times the attitude matrix, its first two rows (the third across scan)
-    const double x = qa[0], y = qa[1], z = qa[2], w = qa[3];
-    const double x2 = x + x, y2 = y + y, z2 = z + z;
-    const double al = w * w - z * z, be = x * x - y * y, xy = x2 * y;
-    const double M0[3] = {al + be, xy + z2 * w, x2 * z - y2 * w};
-    const double M1[3] = {xy - z2 * w, al - be, y2 * z + x2 * w};
-    const double S0 = dot3(M0, uu), S1 = dot3(M1, uu);
-    double m[3], kap;
-    if (AC && ac) {
-        const double M2[3] = {x2 * z + y2 * w, y2 * z - x2 * w, (w * w + z * z) - (x * x + y * y)};
-        const double S2 = dot3(M2, uu);
-        const double rho2 = S0 * S0 + S1 * S1;
-        const double irho = rsqrt_nr(rho2);
-        const double q = S2 * irho, q2 = q * q;
-        const double zeta = fabs(q) < 1e-2
-                                ? q * (1.0 + q2 * (-1.0 / 3.0 + q2 * (1.0 / 5.0 + q2 * (-1.0 / 7.0 + q2 * (1.0 / 9.0)))))
-                                : far_angle(S2, rho2 * irho);
-        R = obs - zeta;
-        const double n0 = -S2 * S0, n1 = -S2 * S1;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) m[c] = M0[c] * n0 + M1[c] * n1 + M2[c] * rho2;
-        kap = nuu * irho * rcp_nr(rho2 + S2 * S2);
-    } else {
-        // eta = phi - f Gamma_c / 2 with f = sign(phi): rotate (x, y) by -f Gamma_c/2
-        const double sg = copysign_of(k.sin_half_gamma, S1);
-        const double xr = S0 * k.cos_half_gamma + S1 * sg;
-        const double yr = S1 * k.cos_half_gamma - S0 * sg;
-        if (__builtin_expect(xr > 0.0 && fabs(yr) < 1e-2 * xr, 1)) {
-            const double ix = rcp_nr(xr);
-            const double q = yr * ix, q2 = q * q;
-            const double eta = q + q * (q2 * (-1.0 / 3.0 + q2 * (1.0 / 5.0 + q2 * (-1.0 / 7.0 + q2 * (1.0 / 9.0)))));
-            R = obs - eta + copysign_of(k.half_gamma_err, S1);
-            kap = nuu * (ix * ix) * (1.0 - q2 * (1.0 - q2 * (1.0 - q2)));
-        } else {
-            const double phi = far_angle(S1, S0);
-            R = obs - (phi >= 0.0 ? phi - k.gamma_half : phi + k.gamma_half);
-            kap = nuu * rcp_nr(S0 * S0 + S1 * S1);
+    const double d2 = d * d;
+    double sd = d * (1.0 - d2 * (1.0 / 6.0 - d2 * (1.0 / 120.0)));
+    double vd = d2 * (0.5 - d2 * (1.0 / 24.0 - d2 * (1.0 / 720.0)));          // 1 - cos d
+    if (__builtin_expect(n > 0, 0)) {
+#pragma unroll 1
+        for (; n > 0; --n) {
+            const double s2 = sd + sd, v2 = s2 * sd;
+            sd = s2 - s2 * vd;
+            vd = v2;
         }
-#pragma unroll
-        for (int c = 0; c < 3; ++c) m[c] = M1[c] * S0 - M0[c] * S1;
     }
-    const double mv = dot3(m, v);
-    const double mu_ = DEFL ? dot3(m, ub) * iub : -mv;
-    const double vp = v[0] * s.p0 + v[1] * s.p1;
-    const double mp = m[0] * s.p0 + m[1] * s.p1;
-    A[0] = (f * mp - mu_ * vp) * kap;
-    A[1] = (f * dot3(m, s.q) - mu_ * dot3(v, s.q)) * kap;
-    A[2] = (f * (rb * dot3(m, s.r) - dot3(m, b)) - mu_ * (rb * dot3(v, s.r))) * (kap * k.eph_r);
-    A[3] = A[0] * tau;
-    A[4] = A[1] * tau;
+    const double cd = 1.0 - vd;
+    sL = kt.sL * cd + kt.cL * sd;
+    cL = kt.cL * cd - kt.sL * sd;
 }
 
-typedef double double4v __attribute__((ext_vector_type(4)));
-__device__ __attribute__((noinline)) inline double4v far_spline(const double* __restrict__ kn, double t) {
-    double B[4];
-    bspline4(kn, t, B);
-    return double4v{B[0], B[1], B[2], B[3]};
-}
-
-// The spline quaternion at t = tau_l + dt from the interval's coefficients a4
-// (x, y, z, w of four knots); kn: tau_{l-2..l+3}, read only when they are not
-// equally spaced.  From the second coefficient by differences, which are small:
-// the sum is rounded once, and so are the B-splines (1 - their sum for the
-// second) only to no effect.
-__device__ __forceinline__ void attitude_at(const double a4[16], const KnotTab& kt, double dt,
-                                            const double* __restrict__ kn, double t, double q[4]) {
-    double b0, b2, b3;
+// The B-splines and the spline quaternion at t = tau_l + dt from the interval's
+// coefficients a4 (x, y, z, w of four knots), as in observe(); kn:
+// tau_{l-2..l+3}, read only when they are not equally spaced.
+__device__ __forceinline__ void spline_at(const double a4[16], const KnotTab& kt, double dt,
+                                          const double* __restrict__ kn, double t, double B[4], double q[4]) {
     if (__builtin_expect(kt.inv_dt > 0.0, 1)) {
-        const double u = dt * kt.inv_dt, w = 1.0 - u, w2 = w * w;
-        b0 = w2 * w * (1.0 / 6.0);
-        b2 = 2.0 / 3.0 - 0.5 * (w2 * (1.0 + u));
-        b3 = u * u * u * (1.0 / 6.0);
+        const double x = dt * kt.inv_dt, x1 = 1.0 - x;
+        const double x2 = x * x, x3 = x2 * x;
+        const double s6 = 1.0 / 6.0;
+        B[0] = x1 * x1 * x1 * s6;
+        B[1] = (3.0 * x3 - 6.0 * x2 + 4.0) * s6;
+        B[2] = (-3.0 * x3 + 3.0 * x2 + 3.0 * x + 1.0) * s6;
+        B[3] = x3 * s6;
     } else {
-        const double4v b = far_spline(kn, t);
-        b0 = b.x;
-        b2 = b.z;
-        b3 = b.w;
+        bspline4(kn, t, B);
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const double a1 = a4[4 + c];
-        q[c] = a1 + (b0 * (a4[c] - a1) + (b2 * (a4[8 + c] - a1) + b3 * (a4[12 + c] - a1)));
+    for (int c = 0; c < 4; ++c) q[c] = a4[c] * B[0] + a4[4 + c] * B[1] + a4[8 + c] * B[2] + a4[12 + c] * B[3];
+}
+
+// What one observation contributes to the A and C blocks.
+struct TimeRow {
+    double R;          // residual eta_obs + c - eta (across scan: zeta_obs - zeta)
+    double g[4];       // dR/dq at the normalised quaternion
+    double q[4];       // sum a_n B_n (not normalised)
+    double D;          // 1 - |q|^2 (eq:Dl)
+    double B[4];       // B_{l-3..l}(t)
+};
+
+// Residual and attitude partials of one observation for the time-ordered
+// pass: the proper direction S as observe() computes it, operation by operation
+// (a calibration's value is the mean of a few residuals, which would show
+// another rounding), then dR/dq = 2 sec(zeta) q^ {S'n, 0} from n sec(zeta) =
+// (-S_z S_x, -S_z S_y, rho^2) / rho^2 without rho: 1 / rho^2 comes from the
+// reciprocal that the angle's quotient took.
+template <bool AC, bool DEFL>
+__device__ __forceinline__ void time_row(const DevConsts& k, const SrcPrep& s, const double a4[16], const KnotTab& kt,
+                                         const double* __restrict__ kn, double t, double obs, bool ac, TimeRow& o) {
+    const double dt = t - kt.tau;
+    double S[3], A[9];
+    double u[3];
+    {
+        double sL, cL;
+        orbit_at(k, kt, dt, sL, cL);
+        const double bx = k.eph_r * cL, by = k.eph_r * sL;
+        const double b[3] = {bx, k.cos_obl * by, k.sin_obl * by};
+        const double tau = (t + dot3(s.r, b) * k.au_c - k.t_ep) * k.inv_year;
+        double ub[3], uu[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) ub[c] = s.r[c] + tau * s.mu[c] - s.plx * b[c];
+        const double iub = rsqrt_nr(dot3(ub, ub));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) uu[c] = ub[c] * iub;
+        if constexpr (DEFL) {
+            // the Sun's light deflection, as in observe()
+            const double ib = rsqrt_nr(dot3(b, b));
+            const double eu = dot3(b, uu) * ib;
+            const double gam = k.defl * ib / (1.0 + eu) * (2.0 + k.gpar[0]);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) uu[c] += gam * (b[c] * ib - eu * uu[c]);
+        }
+        uu[0] -= k.vel * sL;
+        uu[1] += k.vel_co * cL;
+        uu[2] += k.vel_so * cL;
+        const double iuu = rsqrt_nr(dot3(uu, uu));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) u[c] = uu[c] * iuu;
     }
+    spline_at(a4, kt, dt, kn, t, o.B, o.q);
+    const double n2 = o.q[0] * o.q[0] + o.q[1] * o.q[1] + o.q[2] * o.q[2] + o.q[3] * o.q[3];
+    o.D = 1.0 - n2;
+    const double iq = rsqrt_nr(n2);
+    quat2mat_h(o.q, iq * iq, A);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) S[c] = A[3 * c] * u[0] + A[3 * c + 1] * u[1] + A[3 * c + 2] * u[2];
+    const double iq2 = iq + iq;
+    const double qx = o.q[0] * iq2, qy = o.q[1] * iq2, qz = o.q[2] * iq2, qw = o.q[3] * iq2;    // twice the unit quaternion
+    if (AC && ac) {
+        const double rho2 = S[0] * S[0] + S[1] * S[1];
+        const double irho = rsqrt_nr(rho2);
+        double ix, h2;
+        bool near;
+        o.R = obs - angle_of(rho2 * irho, S[2], ix, h2, near);
+        const double m0 = -S[1] * irho, m1 = S[0] * irho;
+        o.g[0] = qz * m1 - qw * m0;
+        o.g[1] = -(qw * m1 + qz * m0);
+        o.g[2] = qy * m0 - qx * m1;
+        o.g[3] = qx * m0 + qy * m1;
+        return;
+    }
+    // eta = phi - f Gamma_c / 2 with f = sign(phi): rotate (x, y) by -f Gamma_c/2
+    const double sg = copysign_of(k.sin_half_gamma, S[1]);
+    const double xr = S[0] * k.cos_half_gamma + S[1] * sg;
+    const double yr = S[1] * k.cos_half_gamma - S[0] * sg;
+    double ix, p2;
+    bool near;
+    o.R = obs - angle_of(xr, yr, ix, p2, near) + copysign_of(k.half_gamma_err, S[1]);
+    const double i2 = __builtin_expect(near, 1) ? (ix * ix) * (1.0 - p2 * (1.0 - p2 * (1.0 - p2)))
+                                                : rcp_nr(S[0] * S[0] + S[1] * S[1]);    // 1 / (S_x^2 + S_y^2)
+    const double h = -S[2] * i2, n0 = h * S[0], n1 = h * S[1];
+    // {q_v, q_w} {n, 0} = {q_w n + q_v x n, -q_v . n}, n_z = 1
+    o.g[0] = qw * n0 + qy - qz * n1;
+    o.g[1] = qw * n1 + qz * n0 - qx;
+    o.g[2] = qw + qx * n1 - qy * n0;
+    o.g[3] = -(qx * n0 + qy * n1 + qz);
 }
 
 // dR/dq = 2 sec(zeta) q {S'n, 0} (eq:dfadq), n of eq:srspqr; across scan
@@ -568,26 +567,29 @@ __device__ __forceinline__ void attitude_partial(const ObsEval& o, double g[4], 
 // non-positive pivot makes its whole row of U zero and counts one rank
 // defect; no pivoting), in right-looking form: each pivot row, once formed,
 // is subtracted from the trailing rows as an outer product.  U holds the
-// upper triangle of N row-major on entry and the factor on exit, with the
-// reciprocals of the pivots (0 for a zero row) on its diagonal: a square root
-// and a division take 105 and 70 cycles here, a reciprocal square root 40.
-// Returns the defect count.
+// upper triangle of N row-major on entry and the factor on exit; returns the
+// defect count.
 template <int NN>
 __device__ __forceinline__ int small_chol_factor(double U[NN * NN]) {
     int d = 0;
 #pragma unroll
     for (int p = 0; p < NN; ++p) {
         const double piv = U[p * NN + p];
-        const double inv = rsqrt_pivot(piv);
-        d += piv > 0.0 ? 0 : 1;
-        U[p * NN + p] = inv;
+        if (piv > 0.0) {
+            const double up = sqrt(piv);
+            U[p * NN + p] = up;
 #pragma unroll
-        for (int c = p + 1; c < NN; ++c) U[p * NN + c] = piv > 0.0 ? U[p * NN + c] * inv : 0.0;
-        // trailing rows r > p, columns c >= r
+            for (int c = p + 1; c < NN; ++c) U[p * NN + c] /= up;
+            // trailing rows r > p, columns c >= r
 #pragma unroll
-        for (int r = p + 1; r < NN; ++r)
+            for (int r = p + 1; r < NN; ++r)
 #pragma unroll
-            for (int c = r; c < NN; ++c) U[r * NN + c] -= U[p * NN + r] * U[p * NN + c];
+                for (int c = r; c < NN; ++c) U[r * NN + c] -= U[p * NN + r] * U[p * NN + c];
+        } else {
+            ++d;
+#pragma unroll
+            for (int c = p; c < NN; ++c) U[p * NN + c] = 0.0;
+        }
     }
     return d;
 }
@@ -601,14 +603,16 @@ __device__ __forceinline__ void small_chol_subst(const double U[NN * NN], double
     // U' y = b
 #pragma unroll
     for (int p = 0; p < NN; ++p) {
-        x[p] = U[p * NN + p] > 0.0 ? x[p] * U[p * NN + p] : 0.0;
+        const double up = U[p * NN + p];
+        x[p] = up > 0.0 ? x[p] / up : 0.0;
 #pragma unroll
         for (int r = p + 1; r < NN; ++r) x[r] -= U[p * NN + r] * x[p];
     }
     // U x = y
 #pragma unroll
     for (int p = NN - 1; p >= 0; --p) {
-        x[p] = U[p * NN + p] > 0.0 ? x[p] * U[p * NN + p] : 0.0;
+        const double up = U[p * NN + p];
+        x[p] = up > 0.0 ? x[p] / up : 0.0;
 #pragma unroll
         for (int r = 0; r < p; ++r) x[r] -= U[r * NN + p] * x[p];
     }

@@ -395,55 +395,96 @@ __device__ void reg_quantile7_pair(const uint64_t (&kr)[KR], int64_t n, int64_t 
 }
 
 // ------------------------------------------------------------- S, pass 0
-template <int G, bool AC, bool DEFL = false>
+template <int G, bool DEFL = false>
 __global__ __launch_bounds__(256, 2) void k_s_rows(DevConsts k, int64_t n_src, const int64_t* __restrict__ off,
                                                    const double* __restrict__ ot, const double* __restrict__ oeta,
                                                    const float* __restrict__ osig, const int32_t* __restrict__ ocell,
                                                    const int32_t* __restrict__ oell,
                                                    const double* __restrict__ knots,
-                                                   const KnotTab* __restrict__ ktab,
-                                                   const double* __restrict__ a, const double* __restrict__ c,
-                                                   const double* __restrict__ s, const double* __restrict__ eps_a2,
+                                                   const KnotTab* __restrict__ ktab, const double* __restrict__ a,
+                                                   const double* __restrict__ c, const double* __restrict__ s,
+                                                   const double* __restrict__ eps_a2, int eps_bucket,
                                                    double* __restrict__ col, int64_t n_obs,
                                                    const int32_t* __restrict__ order) {
     constexpr int GPB = 256 / G;
-    __shared__ __align__(16) char stage[4][STAGE_BYTES];
     const int gl = threadIdx.x % G;
     const int64_t kg = (int64_t)blockIdx.x * GPB + threadIdx.x / G;
-    const bool valid = kg < n_src;
-    const int64_t i = valid ? order[kg] : 0;
-    const int64_t l0 = valid ? off[i] : 0, l1 = valid ? off[i + 1] : 0;
-    const int trips = wave_trips<G>(l0, l1);
-    if (trips == 0) return;                      // the whole wavefront
-    ObsStream<float, true> st{ot, oeta, osig, ocell, oell, a, knots, ktab, c, eps_a2, stage[threadIdx.x >> 6]};
-    st.start(l0 + gl, l1, G);
+    if (kg >= n_src) return;
+    const int64_t i = order[kg];
     const double* si = s + 5 * i;
-    SourceDir sd;
-    source_dir(k, si[0], si[1], si[2], si[3], si[4], sd);
-    st.gather(k, 0);
-    auto record = [&](int u, int64_t l) {
-        double qa[4], sL, cL;
-        st.take(k, u, qa, sL, cL);
-        const double t = st.t[u], obs = st.e[u] + st.cal, ea = st.ea;
-        const bool ac = AC && st.cf[u] >= k.ac_cf0;
-        const double sg = (double)st.s[u];
-        st.advance(k, u);
-        if (l >= l1) return;
-        double A[5], R, tau;
-        source_row<AC, DEFL>(k, sd, qa, sL, cL, t - k.t_ep, obs, ac, A, R, tau);
+    const double alpha = si[0], delta = si[1], plx = si[2], pma = si[3], pmd = si[4];
+    double sa, ca, sd, cd;
+    sincos(alpha, &sa, &ca);
+    sincos(delta, &sd, &cd);
+    const double p[3] = {-sa, ca, 0.0};
+    const double q[3] = {-sd * ca, -sd * sa, cd};
+    const double r[3] = {cd * ca, cd * sa, sd};
+    double mu[3];
+#pragma unroll
+    for (int cc = 0; cc < 3; ++cc) mu[cc] = p[cc] * pma + q[cc] * pmd;
+    const int64_t l1 = off[i + 1];
+    int64_t l = off[i] + gl;
+    // Current observation with its gathers (attitude coefficients, interval
+    // table entry, calibration, excess noise); the next observation's
+    // columns load at the top of an iteration, its gathers after the
+    // current one has been evaluated.
+    double t_c = 0.0, e_c = 0.0, cal_c = 0.0, ea_c = 0.0;
+    float s_c = 1.0f;
+    int32_t ell_c = 3, cf_c = 0;
+    double a_c[16];
+    KnotTab kt_c = {0.0, 1.0, 0.0, 0.0};
+#pragma unroll
+    for (int e = 0; e < 16; ++e) a_c[e] = 0.0;
+    if (l < l1) {
+        t_c = ot[l];
+        e_c = oeta[l];
+        s_c = osig[l];
+        ell_c = oell[l];
+        cf_c = ocell[l];
+        cal_c = c[cf_c >> 1];
+        ea_c = eps_a2[eps_slot(k, cf_c, ell_c - 3)];
+        const double* a4 = a + 4 * (ell_c - 3);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) a_c[e] = a4[e];
+        kt_c = ktab[ell_c - 3];
+    }
+    for (; l < l1; l += G) {
+        const int64_t ln = l + G;
+        const bool more = ln < l1;
+        double t_n = 0.0, e_n = 0.0;
+        float s_n = 1.0f;
+        int32_t cf_n = 0, ell_n = 3;
+        if (more) {
+            t_n = ot[ln];
+            e_n = oeta[ln];
+            s_n = osig[ln];
+            cf_n = ocell[ln];
+            ell_n = oell[ln];
+        }
+        const bool ac = cf_c >= k.ac_cf0;
+        ObsEval o;
+        observe<DEFL>(k, t_c, e_c, cal_c, r, mu, plx, a_c, knots + (ell_c - 2), kt_c, o, ac);
+        double A[5];
+        source_partials(o, p, q, r, A, ac);
+        const double sg = (double)s_c;
 #pragma unroll
         for (int e = 0; e < 3; ++e) col[e * n_obs + l] = A[e];
-        col[3 * n_obs + l] = tau;                // A[3] = A[0] tau, A[4] = A[1] tau
-        col[4 * n_obs + l] = R;
-        col[5 * n_obs + l] = sg * sg + ea;
-    };
-    int64_t l = l0 + gl;
-    for (int it = 0; it < trips; it += OBS_AHEAD) {
+        col[3 * n_obs + l] = o.tau;              // A[3] = A[0] tau, A[4] = A[1] tau
+        col[4 * n_obs + l] = o.R;
+        col[5 * n_obs + l] = sg * sg + ea_c;
+        if (more) {
+            const double* a4 = a + 4 * (ell_n - 3);
 #pragma unroll
-        for (int u = 0; u < OBS_AHEAD; ++u, l += G) {
-            if (it + u >= trips) break;
-            record(u, l);
+            for (int e = 0; e < 16; ++e) a_c[e] = a4[e];
+            kt_c = ktab[ell_n - 3];
+            cal_c = c[cf_n >> 1];
+            ea_c = eps_a2[eps_slot(k, cf_n, ell_n - 3)];
         }
+        t_c = t_n;
+        e_c = e_n;
+        s_c = s_n;
+        cf_c = cf_n;
+        ell_c = ell_n;
     }
 }
 
@@ -1693,19 +1734,17 @@ inline size_t eps_lds_bytes(int64_t cap, int64_t eps_bucket) {
 }  // namespace
 
 #define AGIS_ROWS_LAUNCH(G)                                                                                      \
-    (ctx->k.defl > 0.0 ? (ctx->has_ac ? k_s_rows<G, true, true> : k_s_rows<G, false, true>)                      \
-                       : (ctx->has_ac ? k_s_rows<G, true> : k_s_rows<G, false>))                                 \
-        <<<groups_grid(n_src, 256 / G), 256, 0, ctx->stream>>>(                                                  \
-            ctx->k, n_src, ctx->src_off, ctx->s_t, ctx->s_eta, ctx->s_sig, ctx->s_cell, ctx->s_ell, ctx->knots,  \
-            ctx->ktab, ctx->a, ctx->c, ctx->s, ctx->eps_a2, ctx->rcol, ctx->n_obs, order)
+    (ctx->k.defl > 0.0 ? k_s_rows<G, true> : k_s_rows<G, false>)<<<groups_grid(n_src, 256 / G), 256, 0, ctx->stream>>>( \
+        ctx->k, n_src, ctx->src_off, ctx->s_t, ctx->s_eta, ctx->s_sig, ctx->s_cell, ctx->s_ell, ctx->knots,        \
+        ctx->ktab, ctx->a, ctx->c, ctx->s, ctx->eps_a2, ctx->cfg.eps_bucket, ctx->rcol, col_stride(ctx->n_obs), order)
 #define AGIS_IRLS_LAUNCH(G)                                                                                      \
     if (ctx->cfg.robust == 2)                                                                                    \
         k_s_irls_eps<G><<<groups_grid(n_src, 256 / G), 256, 0, ctx->stream>>>(                                   \
-            n_src, ctx->src_off, ctx->rcol, ctx->n_obs, ctx->vs, ctx->s, ctx->prep, ctx->ds, ctx->qsrc,           \
+            n_src, ctx->src_off, ctx->rcol, col_stride(ctx->n_obs), ctx->vs, ctx->s, ctx->prep, ctx->ds, ctx->qsrc,           \
             ctx->sdef, ctx->svar, order, ctx->src_eps2, ctx->src_D, ac_cells, ctx->k.ac_cf0);                    \
     else                                                                                                         \
         k_s_irls<G><<<groups_grid(n_src, 256 / G), 256, 0, ctx->stream>>>(                                       \
-            n_src, ctx->src_off, ctx->rcol, ctx->n_obs, ctx->vs, ctx->s, ctx->prep, ctx->ds, ctx->qsrc,           \
+            n_src, ctx->src_off, ctx->rcol, col_stride(ctx->n_obs), ctx->vs, ctx->s, ctx->prep, ctx->ds, ctx->qsrc,           \
             ctx->sdef, ctx->svar, order, ac_cells, ctx->k.ac_cf0)
 
 // The HBM-column kernels over launch positions [k0, k0 + n) of the
@@ -1732,13 +1771,13 @@ static void source_solve_columns(agis_ctx* ctx, int64_t k0, int64_t n) {
     const bool pair = ctx->select_pair;
     (ac_cells ? (reg ? (pair ? k_s_sigma<2, true> : k_s_sigma<1, true>) : k_s_sigma<0, true>)
               : (reg ? (pair ? k_s_sigma<2, false> : k_s_sigma<1, false>) : k_s_sigma<0, false>))
-        <<<(unsigned)n_src, 64, 0, ctx->stream>>>(n_src, ctx->src_off, ctx->rcol + 4 * ctx->n_obs, ctx->vs,
+        <<<(unsigned)n_src, 64, 0, ctx->stream>>>(n_src, ctx->src_off, ctx->rcol + 4 * col_stride(ctx->n_obs), ctx->vs,
                                                   select_reg_limit(ctx), order, ac_cells, ctx->k.ac_cf0);
     if (ctx->cfg.robust == 1 && ctx->irls_cache > 0) {
         // the lanes' first records cached in registers across the rounds
 #define AGIS_IRLS_CACHED(G)                                                                                      \
     k_s_irls<G, IRLS_RC><<<groups_grid(n_src, 256 / G), 256, 0, ctx->stream>>>(                                  \
-        n_src, ctx->src_off, ctx->rcol, ctx->n_obs, ctx->vs, ctx->s, ctx->prep, ctx->ds, ctx->qsrc, ctx->sdef,    \
+        n_src, ctx->src_off, ctx->rcol, col_stride(ctx->n_obs), ctx->vs, ctx->s, ctx->prep, ctx->ds, ctx->qsrc, ctx->sdef,    \
         ctx->svar, order, ac_cells, ctx->k.ac_cf0)
         if (ctx->irls_cache == 1) AGIS_IRLS_CACHED(32);
         else AGIS_IRLS_CACHED(64);
@@ -1803,7 +1842,7 @@ void launch_source_update_robust(agis_ctx* ctx) {
     k_s_robust<NT, FC><<<(unsigned)n, NT, lds, ctx->stream>>>(                                                  \
         ctx->k, n, cl.cap, ctx->src_off, ctx->s_t, ctx->s_eta, ctx->s_sig, ctx->s_cell, ctx->s_ell, ctx->knots,    \
         ctx->ktab, ctx->a, ctx->c, ctx->eps_a2, ctx->cfg.eps_bucket, ctx->s, ctx->prep, ctx->ds, ctx->qsrc,        \
-        ctx->sdef, ctx->svar, ctx->src_order + cl.k0, ctx->vs, ctx->rcol, ctx->n_obs)
+        ctx->sdef, ctx->svar, ctx->src_order + cl.k0, ctx->vs, ctx->rcol, col_stride(ctx->n_obs))
         if (from_col) {
             if (cl.nt == 64) AGIS_SROB_LAUNCH(64, true);
             else if (cl.nt == 128) AGIS_SROB_LAUNCH(128, true);
