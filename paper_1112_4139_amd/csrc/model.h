@@ -106,6 +106,25 @@ __device__ __forceinline__ double rcp_nr(double x) {
 __device__ __forceinline__ void bspline4(const double* __restrict__ kn, double t, double B[4]) {
     // knot tau_{l+j} for j = -2..3
     auto tk = [&](int j) { return kn[j + 2]; };
+    // order 2: B_{l-1}, B_l
+    const double h0 = tk(1) - tk(0);
+    const double b2m1 = (tk(1) - t) / h0, b20 = (t - tk(0)) / h0;
+    // order 3: B_{l-2}, B_{l-1}, B_l
+    const double b3m2 = (tk(1) - t) / (tk(1) - tk(-1)) * b2m1;
+    const double b3m1 = (t - tk(-1)) / (tk(1) - tk(-1)) * b2m1 + (tk(2) - t) / (tk(2) - tk(0)) * b20;
+    const double b30 = (t - tk(0)) / (tk(2) - tk(0)) * b20;
+    // order 4: B_{l-3} .. B_l
+    B[0] = (tk(1) - t) / (tk(1) - tk(-2)) * b3m2;
+    B[1] = (t - tk(-2)) / (tk(1) - tk(-2)) * b3m2 + (tk(2) - t) / (tk(2) - tk(-1)) * b3m1;
+    B[2] = (t - tk(-1)) / (tk(2) - tk(-1)) * b3m1 + (tk(3) - t) / (tk(3) - tk(0)) * b30;
+    B[3] = (t - tk(0)) / (tk(3) - tk(0)) * b30;
+}
+
+// The same by reciprocals of the six spans, in fewer registers: for the A/C pass,
+// whose wavefronts per SIMD they limit.
+__device__ __forceinline__ void bspline4_rcp(const double* __restrict__ kn, double t, double B[4]) {
+    // knot tau_{l+j} for j = -2..3
+    auto tk = [&](int j) { return kn[j + 2]; };
     // reciprocals of the orders' spans
     const double i0 = rcp_nr(tk(1) - tk(0)), ia = rcp_nr(tk(1) - tk(-1)), ib = rcp_nr(tk(2) - tk(0));
     const double ja = rcp_nr(tk(1) - tk(-2)), jb = rcp_nr(tk(2) - tk(-1)), jc = rcp_nr(tk(3) - tk(0));
@@ -445,7 +464,7 @@ __device__ __forceinline__ void spline_at(const double a4[16], const KnotTab& kt
         B[2] = (-3.0 * x3 + 3.0 * x2 + 3.0 * x + 1.0) * s6;
         B[3] = x3 * s6;
     } else {
-        bspline4(kn, t, B);
+        bspline4_rcp(kn, t, B);
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) q[c] = a4[c] * B[0] + a4[4 + c] * B[1] + a4[8 + c] * B[2] + a4[12 + c] * B[3];
