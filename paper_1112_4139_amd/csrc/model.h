@@ -421,8 +421,6 @@ __device__ __forceinline__ double angle_of(double x, double y, double& inv_x, do
     return scale * (q + q * (q2 * (-1.0 / 3.0 + q2 * (1.0 / 5.0 + q2 * (-1.0 / 7.0 + q2 * (1.0 / 9.0))))));
 }
 
-__device__ __forceinline__ double copysign_of(double mag, double sgn) { return __builtin_copysign(mag, sgn); }
-
 // Sine and cosine of the observer's orbital longitude d past the interval's
 // start (Taylor series to d^6 for |d| < 1e-2, as in observe(); in a longer
 // interval of a fraction of d, doubled as often: its rounding, 2^n u, enters
@@ -541,12 +539,14 @@ __device__ __forceinline__ void time_row(const DevConsts& k, const SrcPrep& s, c
         return;
     }
     // eta = phi - f Gamma_c / 2 with f = sign(phi): rotate (x, y) by -f Gamma_c/2
-    const double sg = copysign_of(k.sin_half_gamma, S[1]);
+    const bool pos = S[1] >= 0.0;
+    const double sg = pos ? k.sin_half_gamma : -k.sin_half_gamma;
     const double xr = S[0] * k.cos_half_gamma + S[1] * sg;
     const double yr = S[1] * k.cos_half_gamma - S[0] * sg;
     double ix, p2;
     bool near;
-    o.R = obs - angle_of(xr, yr, ix, p2, near) + copysign_of(k.half_gamma_err, S[1]);
+    // (the error of the rounded pair has a sign of its own)
+    o.R = obs - angle_of(xr, yr, ix, p2, near) + (pos ? k.half_gamma_err : -k.half_gamma_err);
     const double i2 = __builtin_expect(near, 1) ? (ix * ix) * (1.0 - p2 * (1.0 - p2 * (1.0 - p2)))
                                                 : rcp_nr(S[0] * S[0] + S[1] * S[1]);    // 1 / (S_x^2 + S_y^2)
     const double h = -S[2] * i2, n0 = h * S[0], n1 = h * S[1];
