@@ -1,5 +1,6 @@
 """The A/C pass's own evaluation of a record (its residual, splines, field angle
-and observer's orbit): basic angles whose rounded half has a negative error.
+and observer's orbit): basic angles whose rounded half has a negative error,
+field angles far outside the series.
 
 The surveys are made for that: a nearly constant attitude, and stars at chosen
 places (phi, zeta) of the scanning frame, so that a record's angles are known
@@ -110,3 +111,19 @@ def test_basic_angle_with_either_rounding(agis_mod, negative):  # noqa: F811
     _, want, got = _updated(agis_mod, w, "calibration")
     assert np.abs((got - want).astype(float)).max() <= 0.25 * abs(err)
 
+
+@pytest.mark.parametrize("lo,hi", [(0.02, 0.1), (0.3, 1.2), (1.4, 1.7), (2.6, 3.1)])
+def test_field_angles_of_any_size(agis_mod, lo, hi):  # noqa: F811
+    """One record of either field in every interval, a pair of cells each: a
+    pair's update is half the difference of its two residuals.  A residual's
+    rounding is that of the direction, 1.5e-16 in RMS (half the figure for two
+    implementations' difference), of an angle up to pi and of its sum with
+    the basic angle, ulp(pi) / sqrt(12) = 1.3e-16 each: 2.4e-16 together; 4e-16
+    allows for 1.7 times that, and half a difference has 1 / sqrt(2) of it."""
+    rng = np.random.default_rng(11)
+    f = np.where(np.arange(4000) % 2 == 0, 1.0, -1.0)
+    w = _survey(12, synth.knot_sequence(0.0, 3000 * 1200.0, 1200.0), f * rng.uniform(lo, hi, f.size),
+                rng.uniform(-0.05, 0.05, f.size), lambda j: 2, gamma_c=0.02, own_cells=True)
+    _, want, got = _updated(agis_mod, w, "calibration")
+    d = (got - want).astype(float)
+    assert np.sqrt((d * d).mean()) <= 4e-16 / math.sqrt(2.0)
