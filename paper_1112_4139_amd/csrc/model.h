@@ -120,27 +120,6 @@ __device__ __forceinline__ void bspline4(const double* __restrict__ kn, double t
     B[3] = (t - tk(0)) / (tk(3) - tk(0)) * b30;
 }
 
-// The same by reciprocals of the six spans, in fewer registers: for the A/C pass,
-// whose wavefronts per SIMD they limit.
-__device__ __forceinline__ void bspline4_rcp(const double* __restrict__ kn, double t, double B[4]) {
-    // knot tau_{l+j} for j = -2..3
-    auto tk = [&](int j) { return kn[j + 2]; };
-    // reciprocals of the orders' spans
-    const double i0 = rcp_nr(tk(1) - tk(0)), ia = rcp_nr(tk(1) - tk(-1)), ib = rcp_nr(tk(2) - tk(0));
-    const double ja = rcp_nr(tk(1) - tk(-2)), jb = rcp_nr(tk(2) - tk(-1)), jc = rcp_nr(tk(3) - tk(0));
-    // order 2: B_{l-1}, B_l
-    const double b2m1 = (tk(1) - t) * i0, b20 = (t - tk(0)) * i0;
-    // order 3: B_{l-2}, B_{l-1}, B_l
-    const double b3m2 = (tk(1) - t) * ia * b2m1;
-    const double b3m1 = (t - tk(-1)) * ia * b2m1 + (tk(2) - t) * ib * b20;
-    const double b30 = (t - tk(0)) * ib * b20;
-    // order 4: B_{l-3} .. B_l
-    B[0] = (tk(1) - t) * ja * b3m2;
-    B[1] = (t - tk(-2)) * ja * b3m2 + (tk(2) - t) * jb * b3m1;
-    B[2] = (t - tk(-1)) * jb * b3m1 + (tk(3) - t) * jc * b30;
-    B[3] = (t - tk(0)) * jc * b30;
-}
-
 // Attitude matrix A = S'C of a unit quaternion (eq:quat2mat), row-major.
 __device__ __forceinline__ void quat2mat(const double q[4], double A[9]) {
     const double x = q[0], y = q[1], z = q[2], w = q[3];
@@ -496,7 +475,7 @@ __device__ __forceinline__ void spline_at(const double a4[16], const KnotTab& kt
         B[2] = (-3.0 * x3 + 3.0 * x2 + 3.0 * x + 1.0) * s6;
         B[3] = x3 * s6;
     } else {
-        bspline4_rcp(kn, t, B);
+        bspline4(kn, t, B);
     }
 #pragma unroll
     for (int c = 0; c < 4; ++c) q[c] = a4[c] * B[0] + a4[4 + c] * B[1] + a4[8 + c] * B[2] + a4[12 + c] * B[3];

@@ -1,6 +1,8 @@
 """The A/C pass's own evaluation of a record (its residual, splines, field angle
-and observer's orbit): basic angles whose rounded half has a negative error,
-field angles far outside the series.
+and observer's orbit) where it leaves the fast paths: basic angles whose
+rounded half has a negative error, field angles far outside the series, knots
+that are not equally spaced, and knot intervals over which the observer's
+longitude advances by more than the orbit series takes.
 
 The surveys are made for that: a nearly constant attitude, and stars at chosen
 places (phi, zeta) of the scanning frame, so that a record's angles are known
@@ -112,6 +114,12 @@ def test_basic_angle_with_either_rounding(agis_mod, negative):  # noqa: F811
     assert np.abs((got - want).astype(float)).max() <= 0.25 * abs(err)
 
 
+def _uneven(seed, n_iv, dt):
+    rng = np.random.default_rng(seed)
+    inner = np.concatenate([[0.0], np.cumsum(rng.uniform(0.6, 1.4, n_iv) * dt)])
+    return np.concatenate([np.full(3, inner[0]), inner, np.full(3, inner[-1])])
+
+
 @pytest.mark.parametrize("lo,hi", [(0.02, 0.1), (0.3, 1.2), (1.4, 1.7), (2.6, 3.1)])
 def test_field_angles_of_any_size(agis_mod, lo, hi):  # noqa: F811
     """One record of either field in every interval, a pair of cells each: a
@@ -127,3 +135,33 @@ def test_field_angles_of_any_size(agis_mod, lo, hi):  # noqa: F811
     _, want, got = _updated(agis_mod, w, "calibration")
     d = (got - want).astype(float)
     assert np.sqrt((d * d).mean()) <= 4e-16 / math.sqrt(2.0)
+
+
+# (knots, |phi| beyond half the basic angle, zeta, across-scan records per interval)
+REGIMES = {
+    "uneven": (_uneven(1, 61, 1200.0), 8e-3, 0.05, 0),
+    "uneven_ac": (_uneven(2, 61, 1200.0), 8e-3, 9e-3, 12),
+    "wide_ac": (synth.knot_sequence(0.0, 40 * 1200.0, 1200.0), 0.6, 1.0, 12),
+    "all_round": (_uneven(3, 24, 2400.0), None, 0.5, 12),
+    "day_long": (synth.knot_sequence(0.0, 33 * 60000.0, 60000.0), 0.05, 0.05, 12),
+    "months_long": (_uneven(4, 9, 8e6), 0.05, 0.05, 12),
+}
+
+
+@pytest.mark.parametrize("regime", list(REGIMES))
+@pytest.mark.parametrize("block", ["attitude", "calibration"])
+def test_updates_off_the_fast_paths(agis_mod, regime, block):  # noqa: F811
+    """An update may differ from the extended-precision oracle's by 1e-3 uas, the
+    parity target of every update, or by ten times the double-precision
+    oracle's own largest deviation from it (two implementations' rounding of
+    the same system, whose maxima over a few hundred coefficients scatter)."""
+    knots, width, tilt, n_ac = REGIMES[regime]
+    rng = np.random.default_rng(21)
+    gamma = 106.5 * synth.DEG
+    f = np.where(np.arange(600) % 2 == 0, 1.0, -1.0)
+    beyond = rng.uniform(-1.0, 1.0, f.size) * (width if width is not None else 0.0)
+    phi = f * (0.5 * gamma + beyond) if width is not None else f * rng.uniform(0.02, math.pi - 0.02, f.size)
+    w = _survey(22, knots, phi, rng.uniform(-tilt, tilt, f.size), lambda j: 61 + j % 9, n_ac, gamma_c=gamma)
+    double, want, got = _updated(agis_mod, w, block)
+    floor = np.abs(double - want).max()
+    assert np.abs(got - want).max() <= max(1e-3 * synth.UAS, 10.0 * floor)
