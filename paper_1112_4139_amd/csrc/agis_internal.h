@@ -53,10 +53,13 @@ struct StatJobs {
     StatJob job[3];
 };
 
+// Block times: each lies between two events of a pool, which neighbouring
+// blocks may share.  An event is recorded anew only when no block's time refers
+// to it, so the pool holds two per block and one more.
 struct Timers {
-    hipEvent_t ev[10][2];
-    hipEvent_t beg[10], end[10];         // the events a block's time lies between (its own or a neighbour's)
-    bool valid[10];
+    static constexpr int BLOCKS = 7, EVENTS = 2 * BLOCKS + 1;
+    hipEvent_t ev[EVENTS];
+    int beg[BLOCKS], end[BLOCKS];        // indices of a block's events, -1: none
 };
 
 }  // namespace agis

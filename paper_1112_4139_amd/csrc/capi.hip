@@ -446,14 +446,12 @@ extern "C" int agis_create(const agis_config_t* cfg, agis_ctx_t** out) {
         ctx->err = "initial copies failed";
         return fail(AGIS_E_DEVICE);
     }
-    for (int e = 0; e < 10; ++e) {
-        ctx->tm.valid[e] = false;
-        for (int k = 0; k < 2; ++k)
-            if (hipEventCreateWithFlags(&ctx->tm.ev[e][k], hipEventDisableSystemFence) != hipSuccess) {
-                ctx->err = "hipEventCreate failed";
-                return fail(AGIS_E_DEVICE);
-            }
-    }
+    for (int b = 0; b < Timers::BLOCKS; ++b) ctx->tm.beg[b] = ctx->tm.end[b] = -1;
+    for (hipEvent_t& ev : ctx->tm.ev)
+        if (hipEventCreateWithFlags(&ev, hipEventDisableSystemFence) != hipSuccess) {
+            ev = nullptr;
+            return fail(set_error(ctx, AGIS_E_DEVICE, "hipEventCreate failed"));
+        }
     *out = ctx;
     return AGIS_OK;
 }
@@ -488,10 +486,8 @@ extern "C" void agis_destroy(agis_ctx_t* ctx) {
         dfree(ctx->mlp_m2[w]);
         dfree(ctx->mlp_g[w]);
     }
-    for (int e = 0; e < 10; ++e) {
-        if (ctx->tm.ev[e][0]) (void)hipEventDestroy(ctx->tm.ev[e][0]);
-        if (ctx->tm.ev[e][1]) (void)hipEventDestroy(ctx->tm.ev[e][1]);
-    }
+    for (hipEvent_t ev : ctx->tm.ev)
+        if (ev) (void)hipEventDestroy(ev);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
 }
@@ -709,25 +705,39 @@ enum { T_S = 0, T_AC = 1, T_BAND = 2, T_CAL = 3, T_FRAME = 4, T_EPS = 5, T_ITER 
 // Times on the stream between events without a system fence (nothing but
 // their time is read).  A record costs a gap of about 4 us between two
 // kernels, so a block that follows another one directly starts at its stop
-// event (tfollow), and an iteration begins and ends with its blocks.
-static void tstart(agis_ctx* ctx, int e) {
+// event (tfollow), and an iteration begins and ends with its blocks (tspan).
+static int tmark(agis_ctx* ctx) {
+    Timers& tm = ctx->tm;
+    for (int e = 0; e < Timers::EVENTS; ++e) {
+        bool used = false;
+        for (int b = 0; b < Timers::BLOCKS; ++b) used |= tm.beg[b] == e || tm.end[b] == e;
+        if (!used) return hipEventRecord(tm.ev[e], ctx->stream) == hipSuccess ? e : -1;
+    }
+    return -1;
+}
+static void tstart(agis_ctx* ctx, int b) {
     if (!ctx->timing) return;
-    (void)hipEventRecord(ctx->tm.ev[e][0], ctx->stream);
-    ctx->tm.beg[e] = ctx->tm.ev[e][0];
+    ctx->tm.end[b] = -1;
+    ctx->tm.beg[b] = tmark(ctx);
 }
-static void tfollow(agis_ctx* ctx, int e, int prev) {
-    if (ctx->timing) ctx->tm.beg[e] = ctx->tm.ev[prev][1];
-}
-static void tstop(agis_ctx* ctx, int e) {
+static void tfollow(agis_ctx* ctx, int b, int prev) {
     if (!ctx->timing) return;
-    (void)hipEventRecord(ctx->tm.ev[e][1], ctx->stream);
-    ctx->tm.end[e] = ctx->tm.ev[e][1];
-    ctx->tm.valid[e] = true;
+    ctx->tm.end[b] = -1;
+    ctx->tm.beg[b] = ctx->tm.end[prev];
 }
-static double tget(agis_ctx* ctx, int e) {
-    if (!ctx->tm.valid[e]) return 0.0;
+static void tstop(agis_ctx* ctx, int b) {
+    if (ctx->timing) ctx->tm.end[b] = tmark(ctx);
+}
+static void tspan(agis_ctx* ctx, int b, int first, int last) {
+    if (!ctx->timing) return;
+    ctx->tm.beg[b] = ctx->tm.beg[first];
+    ctx->tm.end[b] = ctx->tm.end[last];
+}
+static double tget(agis_ctx* ctx, int b) {
+    const Timers& tm = ctx->tm;
+    if (tm.beg[b] < 0 || tm.end[b] < 0) return 0.0;
     float ms = 0.0f;
-    if (hipEventElapsedTime(&ms, ctx->tm.beg[e], ctx->tm.end[e]) != hipSuccess) return 0.0;
+    if (hipEventElapsedTime(&ms, tm.ev[tm.beg[b]], tm.ev[tm.end[b]]) != hipSuccess) return 0.0;
     return (double)ms;
 }
 
@@ -962,7 +972,6 @@ extern "C" int agis_frame_apply(agis_ctx_t* ctx, const double eps_omega[6]) {
 static int iterate_once(agis_ctx* ctx, agis_iter_stats_t* st) {
     int rc = run_source(ctx);
     if (rc) return rc;
-    ctx->tm.beg[T_ITER] = ctx->tm.beg[T_S];
     // robust: eps_a from the residuals after the source update (Sect. 5.2.5)
     rc = run_ac(ctx, true, true, true, true, nullptr, true, T_S);
     if (rc) return rc;
@@ -972,9 +981,9 @@ static int iterate_once(agis_ctx* ctx, agis_iter_stats_t* st) {
         launch_frame_apply(ctx);
         HIPCHK(hipGetLastError());
         tstop(ctx, T_FRAME);
-        ctx->tm.end[T_ITER] = ctx->tm.end[T_FRAME];
-        ctx->tm.valid[T_ITER] = ctx->tm.valid[T_FRAME];
+        tspan(ctx, T_ITER, T_S, T_FRAME);
     } else {
+        tspan(ctx, T_ITER, T_S, T_S);
         tstop(ctx, T_ITER);
     }
     if (st) {
