@@ -226,6 +226,17 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 constexpr int AC_ROW = 25, AC_B = 7;
 constexpr int AC_ROW_MIXED = 33;
 
+// Slots of an interval of n records, and how many of a chunk's 64 lie before
+// slot `end`.  Unsigned: a range may hold every record of a survey, up to 2^31 -
+// 1, and its slots, and the chunk after them, reach past 2^31.
+__host__ __device__ constexpr uint32_t ac_slots(uint32_t n) { return (n + 3) & ~3u; }
+__host__ __device__ constexpr int ac_left(uint32_t end, uint32_t base) {
+    return end - base < 64 ? (int)(end - base) : 64;
+}
+constexpr uint32_t AC_MOST = ac_slots(0x7FFFFFFFu) + 4 * 8;
+static_assert(ac_slots(0x7FFFFFFFu) == 0x80000000u && ac_left(AC_MOST, 0) == 64 && ac_left(AC_MOST, AC_MOST - 4) == 4 &&
+              AC_MOST + 128 > AC_MOST, "the slots of the largest survey");
+
 // The A/C pass's gathers, one chunk of 64 records ahead.
 struct AcRecord {
     double t, e, cal, ea;
@@ -292,23 +303,24 @@ __global__ __launch_bounds__(64, MIXED ? 2 : 3) void k_ac_pass(DevConsts k, int6
     // four on: no step of four observations spans two intervals.  Lane i holds
     // the end of interval i's slots, what turns its slots into observations
     // counted from the range's first, and the end of these.
-    int ends = 0, shift, stop;
+    uint32_t ends, shift, stop;
     {
         const int64_t jl = j0 + (lane < count ? lane : count - 1);
-        const int start = (int)(iv_off[jl] - first);
-        stop = (int)(iv_off[jl + 1] - first);
-        const int slots = lane < count ? (stop - start + 3) & ~3 : 0;
+        const uint32_t start = (uint32_t)(iv_off[jl] - first);
+        stop = (uint32_t)(iv_off[jl + 1] - first);
+        const uint32_t slots = lane < count ? ac_slots(stop - start) : 0;
         ends = slots;
 #pragma unroll
         for (int m = 1; m < RANGE; m <<= 1) {
-            const int below = __shfl_up(ends, m, 64);
+            const uint32_t below = __shfl_up(ends, m, 64);
             ends += lane >= m ? below : 0;
         }
         shift = start - (ends - slots);
     }
     if (lane < 4 * (count + 3)) sh_a[lane] = a[4 * j0 + lane];
     if (lane < 4 * count) sh_k[lane] = reinterpret_cast<const double*>(ktab + j0)[lane];
-    const int n = __builtin_amdgcn_readlane(ends, RANGE - 1);
+    auto lane_of = [](uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+    const uint32_t n = lane_of(ends, RANGE - 1);
     const double lam2x4 = 4.0 * k.lam2;
     const int ri = lane & 15, rk = lane >> 4;
     // this lane's operands of step kk, 4 kk rows on (FP64: a is a product of two
@@ -396,26 +408,26 @@ __global__ __launch_bounds__(64, MIXED ? 2 : 3) void k_ac_pass(DevConsts k, int6
     bool mine_n = false;
     AcRecord g = {};
     int iv_load = 0;                       // interval of the first slot to load
-    auto load = [&](int base) {
-        const int slot = base + lane < n ? base + lane : n - 1;
+    auto load = [&](uint32_t base) {
+        const uint32_t slot = base + lane < n ? base + lane : n - 1;
         iv_n = iv_load;
-        int by = __builtin_amdgcn_readlane(shift, iv_load), past = __builtin_amdgcn_readlane(stop, iv_load);
+        uint32_t by = lane_of(shift, iv_load), past = lane_of(stop, iv_load);
         while (iv_load + 1 < count) {
-            const int end = __builtin_amdgcn_readlane(ends, iv_load);
+            const uint32_t end = lane_of(ends, iv_load);
             if (end > base + 64) break;
             ++iv_load;
             const bool on = slot >= end;
             iv_n = on ? iv_load : iv_n;
-            by = on ? __builtin_amdgcn_readlane(shift, iv_load) : by;
-            past = on ? __builtin_amdgcn_readlane(stop, iv_load) : past;
+            by = on ? lane_of(shift, iv_load) : by;
+            past = on ? lane_of(stop, iv_load) : past;
         }
-        const int at = slot + by;
+        const uint32_t at = slot + by;
         mine_n = at < past && base + lane < n;
         // from a base that the wavefront shares: a slot is at most 3 RANGE
         // further on than its observation
         constexpr int BACK = 4 * RANGE;
         const int64_t from = first + base - BACK;
-        const uint32_t l = (uint32_t)((at < past ? at : past - 1) - (base - BACK));
+        const uint32_t l = (at < past ? at : past - 1) - base + BACK;
         auto column = [&](auto* p) {
             return *reinterpret_cast<decltype(p)>(reinterpret_cast<const char*>(p + from) + (uint32_t)(l * sizeof(*p)));
         };
@@ -444,7 +456,7 @@ __global__ __launch_bounds__(64, MIXED ? 2 : 3) void k_ac_pass(DevConsts k, int6
         gather();
         if (n > 64) load(64);
     }
-    for (int base = 0; base < n; base += 64) {
+    for (uint32_t base = 0; base < n; base += 64) {
         const bool ac = AC && g.cf >= k.ac_cf0;
         TimeRow o;
         {
@@ -548,7 +560,7 @@ __global__ __launch_bounds__(64, MIXED ? 2 : 3) void k_ac_pass(DevConsts k, int6
             if (base + 128 < n) load(base + 128);
             // groups of four observations past the interval's end hold padding
             // rows of weight zero: their matrix-core steps would add zeros
-            const int steps = n - base < 64 ? (n - base + 3) >> 2 : 16;
+            const int steps = (ac_left(n, base) + 3) >> 2;
             float4_t Ck = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int kk = 0; kk < 16; ++kk) {
@@ -567,7 +579,7 @@ __global__ __launch_bounds__(64, MIXED ? 2 : 3) void k_ac_pass(DevConsts k, int6
             // operands of four steps in registers while the next four load (their
             // latency, up to 300 clocks, is longer than a step's product, 64)
             double av[4], zv[4], bv[4], an[4], zn[4], bn[4];
-            int end = __builtin_amdgcn_readlane(ends, now) - base;
+            int end = ac_left(lane_of(ends, now), base);
             auto fetch = [&](int q, double x[4], double z[4], double y[4]) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
@@ -589,7 +601,7 @@ __global__ __launch_bounds__(64, MIXED ? 2 : 3) void k_ac_pass(DevConsts k, int6
                         // the interval's sums are complete (and empty ones')
                         while (row + 4 * u >= end && now + 1 < count) {
                             flush();
-                            end = __builtin_amdgcn_readlane(ends, now) - base;
+                            end = ac_left(lane_of(ends, now), base);
                         }
                         if (row + 4 * u < end) C = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u], y[u], C, 0, 0, 0);
                     }
