@@ -243,6 +243,8 @@ struct agis_ctx {
 
     // lanes per source in the S block
     int s_group = 16;
+    int32_t ac_range = 1;                // knot intervals per wavefront of the A/C pass
+    int32_t ac_range_forced = 0;         // ... 1 to 8: whatever the observations
     int64_t select_reg_limit = INT64_MAX;   // robust quantiles: register-held keys up to this count
     int64_t select_reg_min_mean = 256;      // ... in the register kernel from this mean set size
     bool select_pair = true;                // ... both intersextile order statistics in one set of passes
@@ -327,3 +329,7 @@ void launch_residuals(agis_ctx* ctx, double* R_input_order);
 void launch_stats(agis_ctx* ctx, const StatJobs& jobs, int n_jobs, double* out);
 
 }  // namespace agis
+
+// Knot intervals per wavefront of the A/C pass for intervals of observations
+// off[j] .. off[j + 1] (exported for the test of its rule).
+extern "C" int32_t agis_ac_pass_range(int64_t n_intervals, const int64_t* off);

@@ -362,6 +362,7 @@ extern "C" int agis_create(const agis_config_t* cfg, agis_ctx_t** out) {
         k.inv_bucket = 1.0 / cfg->eps_bucket;
     }
     if (const char* e = std::getenv("AGIS_S_GROUP")) ctx->s_group = std::atoi(e);
+    if (const char* e = std::getenv("AGIS_AC_RANGE")) ctx->ac_range_forced = std::min(std::max(std::atoi(e), 0), 8);
     if (const char* e = std::getenv("AGIS_SELECT_REG_LIMIT")) ctx->select_reg_limit = std::atoll(e);
     if (const char* e = std::getenv("AGIS_SELECT_REG_MIN_MEAN")) ctx->select_reg_min_mean = std::atoll(e);
     if (const char* e = std::getenv("AGIS_SELECT_PAIR")) ctx->select_pair = std::atoi(e) != 0;

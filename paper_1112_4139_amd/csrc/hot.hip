@@ -23,6 +23,7 @@
 // Each lane walks its item's observations with stride G and loads the next
 // observation's columns while the current one is evaluated.  No global
 // atomics; all sums have a fixed order.
+#include <algorithm>
 #include <type_traits>
 
 #include "agis_internal.h"
@@ -254,14 +255,17 @@ struct AcRecord {
 //        -W (g R - 2 lambda^2 q D) (4), W, W R)
 // and the interval's sums are blocks of C = sum over observations of a b'
 // (16 x 16): pairs x entries (eq:normAmod), B_n x right-hand side, and
-// fov x (W, W R) for eq:normC.  One wavefront takes RANGE neighbouring knot
-// intervals, 64 observations at a time (one per lane), writes b and the factors
+// fov x (W, W R) for eq:normC.  One wavefront takes `range` (at most RANGE)
+// neighbouring knot intervals, 64 observations at a time (one per lane), writes b and the factors
 // of a to LDS and feeds them to v_mfma_f64_16x16x4 steps of four observations
-// of one interval each.
+// of one interval each, in an order that does not depend on the range (nor do
+// the sums).
 //
-// An interval has 15 to 300 observations: one interval per wavefront leaves 29%
-// to 88% of the lanes' slots filled and starts the loads anew each time; over
-// eight they follow on (97%; 4 and 16 intervals: 4% and 2% slower).  A SIMD's
+// An interval of 15 to 300 observations by itself leaves 29% to 88% of the
+// lanes' slots filled and starts the loads anew each time; over eight they
+// follow on (97%; 4 and 16 intervals: 4% and 2% slower at 8 million intervals).
+// Fewer intervals with more records each are shared out more evenly in
+// shorter ranges: agis_ac_pass_range below.  A SIMD's
 // FP64 products and FP64 arithmetic share a pipe within a wavefront but not
 // between them, and no unit is busy for more than half of the time: latencies
 // bound it, at three wavefronts per SIMD (168 registers, 13 KB).  1M sources,
@@ -286,7 +290,7 @@ __global__ __launch_bounds__(64, MIXED ? 2 : 3) void k_ac_pass(DevConsts k, int6
                                                    const double* __restrict__ knots,
                                                    const KnotTab* __restrict__ ktab, const double* __restrict__ a,
                                                    const double* __restrict__ c, const double* __restrict__ eps_a2,
-                                                   int robust, double* __restrict__ iv_sums,
+                                                   int robust, int range, double* __restrict__ iv_sums,
                                                    double* __restrict__ iv_cal, double* __restrict__ wr_out,
                                                    const int32_t* __restrict__ wr_pos) {
     static_assert(!MIXED || RANGE == 1, "the FP64 sums of mixed precision belong to one interval");
@@ -296,8 +300,8 @@ __global__ __launch_bounds__(64, MIXED ? 2 : 3) void k_ac_pass(DevConsts k, int6
     __shared__ __align__(16) double sh_a[4 * (RANGE + 3)];
     __shared__ __align__(16) double sh_k[4 * RANGE];
     const int lane = threadIdx.x;
-    const int64_t j0 = (int64_t)blockIdx.x * RANGE;
-    const int count = (int)(K - j0 < RANGE ? K - j0 : RANGE);
+    const int64_t j0 = (int64_t)blockIdx.x * range;
+    const int count = (int)(K - j0 < range ? K - j0 : range);
     const int64_t first = iv_off[j0];
     // Slots for the range's observations, each interval's from a multiple of
     // four on: no step of four observations spans two intervals.  Lane i holds
@@ -320,7 +324,7 @@ __global__ __launch_bounds__(64, MIXED ? 2 : 3) void k_ac_pass(DevConsts k, int6
     if (lane < 4 * (count + 3)) sh_a[lane] = a[4 * j0 + lane];
     if (lane < 4 * count) sh_k[lane] = reinterpret_cast<const double*>(ktab + j0)[lane];
     auto lane_of = [](uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
-    const uint32_t n = lane_of(ends, RANGE - 1);
+    const uint32_t n = lane_of(ends, count - 1);
     const double lam2x4 = 4.0 * k.lam2;
     const int ri = lane & 15, rk = lane >> 4;
     // this lane's operands of step kk, 4 kk rows on (FP64: a is a product of two
@@ -855,22 +859,22 @@ void launch_source_update(agis_ctx* ctx) {
     }
 }
 
-// Knot intervals per wavefront of the A/C pass.
+// Knot intervals per wavefront of the A/C pass, at most.
 constexpr int AC_RANGE = 8;
 
-template <int RANGE, typename KERN, typename T>
-static void ac_launch(agis_ctx* ctx, KERN kern, const T* sig) {
-    kern<<<(unsigned)((ctx->K + RANGE - 1) / RANGE), 64, 0, ctx->stream>>>(
+template <typename KERN, typename T>
+static void ac_launch(agis_ctx* ctx, KERN kern, int range, const T* sig) {
+    kern<<<(unsigned)((ctx->K + range - 1) / range), 64, 0, ctx->stream>>>(
         ctx->k, ctx->K, ctx->iv_off, ctx->t_t, ctx->t_eta, sig, ctx->t_cellfov, ctx->t_src, ctx->prep, ctx->knots,
-        ctx->ktab, ctx->a, ctx->c, ctx->eps_a2, robust_now(ctx), ctx->iv_sums, ctx->iv_cal,
+        ctx->ktab, ctx->a, ctx->c, ctx->eps_a2, robust_now(ctx), range, ctx->iv_sums, ctx->iv_cal,
         ctx->geo_ccds > 0 ? ctx->geo_wr : nullptr, ctx->geo_pos);
 }
 
 template <bool ROBUST, typename T>
 static void ac_pass_with(agis_ctx* ctx, const T* sig) {
     if (ctx->cfg.precision == AGIS_MIXED) {
-        ac_launch<1>(ctx, ctx->has_ac ? k_ac_pass<true, true, T, false, ROBUST, 1>
-                                      : k_ac_pass<true, false, T, false, ROBUST, 1>, sig);
+        ac_launch(ctx, ctx->has_ac ? k_ac_pass<true, true, T, false, ROBUST, 1>
+                                   : k_ac_pass<true, false, T, false, ROBUST, 1>, 1, sig);
         return;
     }
     auto kern = ctx->has_ac ? k_ac_pass<false, true, T, false, ROBUST, AC_RANGE>
@@ -882,7 +886,7 @@ static void ac_pass_with(agis_ctx* ctx, const T* sig) {
             kern = ctx->has_ac ? k_ac_pass<false, true, T, true, ROBUST, AC_RANGE>
                                : k_ac_pass<false, false, T, true, ROBUST, AC_RANGE>;
     }
-    ac_launch<AC_RANGE>(ctx, kern, sig);
+    ac_launch(ctx, kern, ctx->ac_range, sig);
 }
 
 void launch_ac_pass(agis_ctx* ctx) {
@@ -903,3 +907,38 @@ void launch_band_solve(agis_ctx* ctx) {
 }
 
 }  // namespace agis
+
+// Knot intervals per wavefront of the FP64 A/C pass: 1, 2, 4 or 8, whichever
+// takes least by this count.  A wavefront takes the chunks of 64 slots that its
+// intervals' observations fill, and about two more to start and end; the device
+// holds 3 x 1,024 wavefronts, and the longest runs on while it empties, nine
+// tenths of its time.  Long ranges win where intervals are many and short, by
+// fewer and fuller chunks; short ones where they are few and long, by sharing
+// out evenly.  Measured (ms for ranges of 1, 2, 4, 8; the choice in brackets):
+//   4,383 intervals of 6,099 records   [0.737] 0.863  1.197  1.634
+//   17,532 of 1,525                    [0.615] 0.627  0.715  0.841
+//   39,447 of 678                       0.632 [0.603] 0.624  0.706
+//   39,447 of 113                       0.153  0.134 [0.130] 0.138
+//   473,364 of 141                      2.039  1.749  1.652 [1.625]
+//   17,532 of 17                        0.042  0.027  0.028 [0.025]
+// Eleven other shapes: at most 1.2% more than the best.
+extern "C" int32_t agis_ac_pass_range(int64_t n_intervals, const int64_t* off) {
+    int32_t best = 1;
+    double least = 0.0;
+    for (int32_t r = 1; r <= agis::AC_RANGE; r *= 2) {
+        int64_t total = 0, longest = 0;
+        for (int64_t j0 = 0; j0 < n_intervals; j0 += r) {
+            int64_t slots = 0;
+            for (int64_t j = j0; j < std::min(j0 + r, n_intervals); ++j) slots += (off[j + 1] - off[j] + 3) & ~int64_t(3);
+            const int64_t chunks = (slots + 63) / 64 + 2;
+            total += chunks;
+            longest = std::max(longest, chunks);
+        }
+        const double time = (double)total / 3072.0 + 0.9 * (double)longest;
+        if (r == 1 || time < least) {
+            best = r;
+            least = time;
+        }
+    }
+    return best;
+}

@@ -390,12 +390,15 @@ int build_store(agis_ctx* ctx, const agis_obs_soa_t* obs, int where) {
                                          flags);
     HIPCHK(hipGetLastError());
     std::vector<int32_t> h_ivc(2 * ctx->K);
+    std::vector<int64_t> h_off(ctx->K + 1);
+    HIPCHK(hipMemcpyAsync(h_off.data(), ctx->iv_off, (ctx->K + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(h_ivc.data(), ctx->iv_cell, 2 * ctx->K * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipMemcpyAsync(&hflags, flags, sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (hflags)
         return set_error(ctx, AGIS_E_SHAPE,
                          "observations of one field of view within one knot interval belong to different cells");
+    ctx->ac_range = ctx->ac_range_forced > 0 ? ctx->ac_range_forced : agis_ac_pass_range(ctx->K, h_off.data());
     // each cell must cover one contiguous run of intervals
     std::vector<int32_t> h_civ(2 * ctx->n_cells, -1);
     std::vector<int32_t> last_seen(ctx->n_cells, -2);
