@@ -222,9 +222,11 @@ typedef float float4_t __attribute__((ext_vector_type(4)));
 
 // A row of the transposition buffer.  FP64: B_0..B_3, 1, [fov +1], [fov -1],
 // then b; the reading lanes form a's products, so that three wavefronts' buffers
-// per SIMD fit a compute unit's LDS.  Mixed precision: a, then b.  (Odd strides:
-// no bank conflicts.)
-constexpr int AC_ROW = 25, AC_B = 7;
+// per SIMD fit a compute unit's LDS (160 KB in granules of 1,280 bytes: two
+// doubles more a row leave room for 11 blocks instead of 12, and cost 1.5% to 3%,
+// 111M records 2.78 ms instead of 2.71).  Mixed precision: a, then b.  (Odd
+// strides, in doubles: no bank conflicts between the rows' writes.)
+constexpr int AC_ROW = 23, AC_B = 7;
 constexpr int AC_ROW_MIXED = 33;
 
 // Slots of an interval of n records, and how many of a chunk's 64 lie before
@@ -263,16 +265,17 @@ struct AcRecord {
 //
 // An interval of 15 to 300 observations by itself leaves 29% to 88% of the
 // lanes' slots filled and starts the loads anew each time; over eight they
-// follow on (97%; 4 and 16 intervals: 4% and 2% slower at 8 million intervals).
+// follow on (97%; 4 and 16 intervals: 4% and 2% slower at 1.6 million intervals).
 // Fewer intervals with more records each are shared out more evenly in
 // shorter ranges: agis_ac_pass_range below.  A SIMD's
 // FP64 products and FP64 arithmetic share a pipe within a wavefront but not
 // between them, and no unit is busy for more than half of the time: latencies
-// bound it, at three wavefronts per SIMD (168 registers, 13 KB).  1M sources,
-// 223M observations: 7.04 -> 5.29 ms (27 bytes of columns and, by source, a
-// seventh of a 64-byte record per observation; two wavefronts 5.9; the next
-// columns asked for before the rows are written 5.37; 12 of 16 blocks by
-// v_mfma_f64_4x4x4, whose operands take two more reads, 5.49).
+// bound it, at three wavefronts per SIMD (168 registers and 12 bytes of scratch a
+// lane, robust 100; 12.4 KB).  1M sources, 223M observations: 7.65 -> 5.17 ms (27
+// bytes of columns and, by source, a seventh of a 64-byte record per
+// observation; variants, against 5.29 before the shorter rows: two wavefronts
+// 5.9; the next columns asked for before the rows are written 5.37; 12 of 16
+// blocks by v_mfma_f64_4x4x4, whose operands take two more reads, 5.49).
 //
 // Mixed precision (MIXED): the model stays FP64; a and b are formed in FP32
 // from single-precision partials, each 64-observation chunk is summed by
@@ -299,6 +302,8 @@ __global__ __launch_bounds__(64, MIXED ? 2 : 3) void k_ac_pass(DevConsts k, int6
     __shared__ __align__(16) XT xw[64][ROW];
     __shared__ __align__(16) double sh_a[4 * (RANGE + 3)];
     __shared__ __align__(16) double sh_k[4 * RANGE];
+    static_assert(MIXED || 12 * ((sizeof(xw) + sizeof(sh_a) + sizeof(sh_k) + 1279) / 1280) <= 128,
+                  "twelve wavefronts in a compute unit's LDS");
     const int lane = threadIdx.x;
     const int64_t j0 = (int64_t)blockIdx.x * range;
     const int count = (int)(K - j0 < range ? K - j0 : range);
