@@ -344,11 +344,9 @@ extern "C" int agis_create(const agis_config_t* cfg, agis_ctx_t** out) {
     k.eph_Lrate = cfg->eph_Lrate;
     k.cos_obl = std::cos(cfg->eps_obl);
     k.sin_obl = std::sin(cfg->eps_obl);
-    k.au_r = k.au_c * k.eph_r;
     k.vel = k.eph_r * k.eph_Lrate * k.au_c;
     k.vel_co = k.vel * k.cos_obl;
     k.vel_so = k.vel * k.sin_obl;
-    k.one_vel2 = 1.0 + k.vel * k.vel;
     k.cos_half_gamma = std::cos(k.gamma_half);
     k.sin_half_gamma = std::sin(k.gamma_half);
     k.half_gamma_err = (double)((long double)k.gamma_half -

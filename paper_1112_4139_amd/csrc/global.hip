@@ -26,7 +26,7 @@ __global__ __launch_bounds__(64) void k_g_pass(DevConsts k, int64_t K, const int
                                                const int32_t* __restrict__ osrc, const SrcPrep* __restrict__ prep,
                                                const double* __restrict__ knots, const KnotTab* __restrict__ ktab,
                                                const double* __restrict__ a, const double* __restrict__ c,
-                                               const double* __restrict__ eps_a2, int eps_bucket, int robust,
+                                               const double* __restrict__ eps_a2, int robust,
                                                double* __restrict__ out) {
     const int lane = threadIdx.x;
     const int64_t j = blockIdx.x;
@@ -97,7 +97,7 @@ void launch_global_solve(agis_ctx* ctx) {
     const bool frozen = ctx->frozen;
 #define AGIS_G_ARGS(SIG)                                                                                           \
     ctx->k, ctx->K, ctx->iv_off, ctx->t_t, ctx->t_eta, SIG, ctx->t_cellfov, ctx->t_src, ctx->prep, ctx->knots,      \
-        ctx->ktab, ctx->a, ctx->c, ctx->eps_a2, ctx->cfg.eps_bucket, frozen ? 0 : robust_now(ctx), ctx->g_iv
+        ctx->ktab, ctx->a, ctx->c, ctx->eps_a2, frozen ? 0 : robust_now(ctx), ctx->g_iv
     if (frozen)
         k_g_pass<double><<<(unsigned)ctx->K, 64, 0, ctx->stream>>>(AGIS_G_ARGS(ctx->t_sig_eff));
     else

@@ -8,11 +8,12 @@
 //                       runs Algorithms C1-C3 on the 5x5 system and applies
 //                       the update.
 //   k_ac_pass           A/C accumulation (Sect. 5.2.1, 5.2.4, 5.3).  One
-//                       wavefront per eight knot intervals streams the time-ordered
-//                       store at (s^(k+1), a^(k), c^(k)) and sums, on the FP64
-//                       matrix cores, the 10 block pairs x 10 unique entries
-//                       of eq:normAmod, its 16 right-hand-side entries and the
-//                       per-fov calibration sums of eq:normC.
+//                       wavefront per one to eight knot intervals streams
+//                       the time-ordered store at (s^(k+1), a^(k), c^(k)) and
+//                       sums, on the FP64 matrix cores, the 10 block pairs x
+//                       10 unique entries of eq:normAmod, its 16
+//                       right-hand-side entries and the per-fov calibration
+//                       sums of eq:normC.
 //   k_band_solve        A solve (Sect. 5.2.2, App. C): one wavefront per
 //                       segment; right-looking modified band Cholesky
 //                       (Algorithm C1 with C2 folded in) as a moving 16x16
@@ -702,13 +703,13 @@ constexpr int BAND_BACK = 8;            // factor blocks in flight on the way ba
 // C3 runs back up the segment: each 16-lane row forms the product of its
 // factor row with the known unknowns, the 4x4 triangle is solved by all lanes.
 //
-// Bound by the instruction issue of the serial chain (about 150 instructions
+// Bound by the instruction issue of the serial chain (about 170 instructions
 // per coefficient forward, 110 back): a segment's time is its length, whatever
 // else runs, until there are several segments per SIMD.  Before, one 16-lane
 // row per segment, per scalar pivot 15 shifted and 15 broadcast rank-1 columns
 // and the entering row summed from an LDS ring took 1340 us for 110 segments
 // of 264 intervals, 1726 us for 12,138 of 154; this form takes 184 and 920 us.
-__global__ __launch_bounds__(64) void k_band_solve(int64_t nseg, const SegDesc* __restrict__ segs,
+__global__ __launch_bounds__(64) void k_band_solve(const SegDesc* __restrict__ segs,
                                                    const double* __restrict__ iv_sums, double* __restrict__ ufac,
                                                    double* __restrict__ yfac, double* __restrict__ da,
                                                    int32_t* __restrict__ seg_def) {
@@ -907,7 +908,7 @@ void launch_ac_pass(agis_ctx* ctx) {
 void launch_band_solve(agis_ctx* ctx) {
     const int64_t nseg = (int64_t)ctx->h_segs.size();
     if (nseg == 0) return;
-    k_band_solve<<<(unsigned)nseg, 64, 0, ctx->stream>>>(nseg, ctx->segs, ctx->iv_sums, ctx->ufac, ctx->yfac, ctx->da,
+    k_band_solve<<<(unsigned)nseg, 64, 0, ctx->stream>>>(ctx->segs, ctx->iv_sums, ctx->ufac, ctx->yfac, ctx->da,
                                                          ctx->seg_def);
 }
 

@@ -27,9 +27,8 @@ struct DevConsts {
     int64_t n_buckets;                       // excess-noise buckets per component (robust)
     double defl;                             // 0, or GM_sun / (c^2 AU) [rad AU]: the Sun's light deflection
     const double* gpar;                      // device [2]: g0 (gamma = 1 + g0), g1 (held at zero)
-    // products of the ephemeris constants: radius in light time [s], orbital
-    // speed over c and its components' factors, 1 + (speed / c)^2
-    double au_r, vel, vel_co, vel_so, one_vel2;
+    // orbital speed over c and its components' factors
+    double vel, vel_co, vel_so;
     double inv_bucket;                       // 1 / (knot intervals per excess-noise bucket) (robust)
 };
 
@@ -491,9 +490,8 @@ struct TimeRow {
 };
 
 // Residual and attitude partials of one observation for the time-ordered
-// pass: the proper direction S as observe() computes it, operation by operation
-// (a calibration's value is the mean of a few residuals, which would show
-// another rounding), then dR/dq = 2 sec(zeta) q^ {S'n, 0} from n sec(zeta) =
+// pass: the proper direction S by observe()'s formulas (equal to rounding: the
+// velocity's constants and the deflection's are multiplied beforehand), then dR/dq = 2 sec(zeta) q^ {S'n, 0} from n sec(zeta) =
 // (-S_z S_x, -S_z S_y, rho^2) / rho^2 without rho: 1 / rho^2 comes from the
 // reciprocal that the angle's quotient took.
 template <bool AC, bool DEFL>

@@ -403,8 +403,7 @@ __global__ __launch_bounds__(256, 2) void k_s_rows(DevConsts k, int64_t n_src, c
                                                    const double* __restrict__ knots,
                                                    const KnotTab* __restrict__ ktab, const double* __restrict__ a,
                                                    const double* __restrict__ c, const double* __restrict__ s,
-                                                   const double* __restrict__ eps_a2, int eps_bucket,
-                                                   double* __restrict__ col, int64_t n_obs,
+                                                   const double* __restrict__ eps_a2, double* __restrict__ col, int64_t n_obs,
                                                    const int32_t* __restrict__ order) {
     constexpr int GPB = 256 / G;
     const int gl = threadIdx.x % G;
@@ -844,7 +843,7 @@ __global__ __launch_bounds__(64) void k_freeze_sigma(DevConsts k, int64_t K, con
                                                      const double* __restrict__ knots,
                                                      const KnotTab* __restrict__ ktab, const double* __restrict__ a,
                                                      const double* __restrict__ c,
-                                                     const double* __restrict__ eps_a2, int eps_bucket, int robust,
+                                                     const double* __restrict__ eps_a2, int robust,
                                                      double* __restrict__ sig_eff) {
     const int lane = threadIdx.x;
     const int64_t j = blockIdx.x;
@@ -1077,8 +1076,7 @@ __global__ __launch_bounds__(NT) void k_s_robust(DevConsts k, int64_t n_src, int
                                                  const int32_t* __restrict__ ocell, const int32_t* __restrict__ oell,
                                                  const double* __restrict__ knots, const KnotTab* __restrict__ ktab,
                                                  const double* __restrict__ a, const double* __restrict__ c,
-                                                 const double* __restrict__ eps_a2, int eps_bucket,
-                                                 double* __restrict__ s, SrcPrep* __restrict__ prep,
+                                                 const double* __restrict__ eps_a2, double* __restrict__ s, SrcPrep* __restrict__ prep,
                                                  double* __restrict__ ds, double* __restrict__ qsrc,
                                                  int32_t* __restrict__ sdef, double* __restrict__ svar,
                                                  const int32_t* __restrict__ order, double* __restrict__ vs_out,
@@ -1427,7 +1425,7 @@ __global__ __launch_bounds__(64 * W) void k_s_regs(DevConsts k, int64_t n_src, c
                                                    const double* __restrict__ knots,
                                                    const KnotTab* __restrict__ ktab, const double* __restrict__ a,
                                                    const double* __restrict__ c, const double* __restrict__ eps_a2,
-                                                   int eps_bucket, double* __restrict__ s,
+                                                   double* __restrict__ s,
                                                    SrcPrep* __restrict__ prep, double* __restrict__ ds,
                                                    double* __restrict__ qsrc, int32_t* __restrict__ sdef,
                                                    double* __restrict__ svar, const int32_t* __restrict__ order,
@@ -1736,7 +1734,7 @@ inline size_t eps_lds_bytes(int64_t cap, int64_t eps_bucket) {
 #define AGIS_ROWS_LAUNCH(G)                                                                                      \
     (ctx->k.defl > 0.0 ? k_s_rows<G, true> : k_s_rows<G, false>)<<<groups_grid(n_src, 256 / G), 256, 0, ctx->stream>>>( \
         ctx->k, n_src, ctx->src_off, ctx->s_t, ctx->s_eta, ctx->s_sig, ctx->s_cell, ctx->s_ell, ctx->knots,        \
-        ctx->ktab, ctx->a, ctx->c, ctx->s, ctx->eps_a2, ctx->cfg.eps_bucket, ctx->rcol, col_stride(ctx->n_obs), order)
+        ctx->ktab, ctx->a, ctx->c, ctx->s, ctx->eps_a2, ctx->rcol, col_stride(ctx->n_obs), order)
 #define AGIS_IRLS_LAUNCH(G)                                                                                      \
     if (ctx->cfg.robust == 2)                                                                                    \
         k_s_irls_eps<G><<<groups_grid(n_src, 256 / G), 256, 0, ctx->stream>>>(                                   \
@@ -1819,7 +1817,7 @@ void launch_source_update_robust(agis_ctx* ctx) {
 #define AGIS_SREG_LAUNCH(W)                                                                                      \
     k_s_regs<W><<<(unsigned)n, 64 * W, 0, ctx->stream>>>(                                                        \
         ctx->k, n, ctx->src_off, ctx->s_t, ctx->s_eta, ctx->s_sig, ctx->s_cell, ctx->s_ell, ctx->knots, ctx->ktab,  \
-        ctx->a, ctx->c, ctx->eps_a2, ctx->cfg.eps_bucket, ctx->s, ctx->prep, ctx->ds, ctx->qsrc, ctx->sdef,        \
+        ctx->a, ctx->c, ctx->eps_a2, ctx->s, ctx->prep, ctx->ds, ctx->qsrc, ctx->sdef,                              \
         ctx->svar, ctx->src_order + cl.k0, ctx->vs, sreg_rows(ctx))
             switch (cl.nt / 64) {
                 case 1: AGIS_SREG_LAUNCH(1); break;
@@ -1841,7 +1839,7 @@ void launch_source_update_robust(agis_ctx* ctx) {
 #define AGIS_SROB_LAUNCH(NT, FC)                                                                                 \
     k_s_robust<NT, FC><<<(unsigned)n, NT, lds, ctx->stream>>>(                                                  \
         ctx->k, n, cl.cap, ctx->src_off, ctx->s_t, ctx->s_eta, ctx->s_sig, ctx->s_cell, ctx->s_ell, ctx->knots,    \
-        ctx->ktab, ctx->a, ctx->c, ctx->eps_a2, ctx->cfg.eps_bucket, ctx->s, ctx->prep, ctx->ds, ctx->qsrc,        \
+        ctx->ktab, ctx->a, ctx->c, ctx->eps_a2, ctx->s, ctx->prep, ctx->ds, ctx->qsrc,                              \
         ctx->sdef, ctx->svar, ctx->src_order + cl.k0, ctx->vs, ctx->rcol, col_stride(ctx->n_obs))
         if (from_col) {
             if (cl.nt == 64) AGIS_SROB_LAUNCH(64, true);
@@ -1964,7 +1962,7 @@ void launch_freeze_sigma(agis_ctx* ctx) {
     if (ctx->K > 0)
         k_freeze_sigma<<<(unsigned)ctx->K, 64, 0, ctx->stream>>>(
             ctx->k, ctx->K, ctx->iv_off, ctx->t_t, ctx->t_eta, ctx->t_sig, ctx->t_cellfov, ctx->t_src, ctx->prep,
-            ctx->knots, ctx->ktab, ctx->a, ctx->c, ctx->eps_a2, ctx->cfg.eps_bucket, ctx->cfg.robust, ctx->t_sig_eff);
+            ctx->knots, ctx->ktab, ctx->a, ctx->c, ctx->eps_a2, ctx->cfg.robust, ctx->t_sig_eff);
     if (ctx->n_obs > 0) {
         const int64_t b = std::min<int64_t>((ctx->n_obs + 255) / 256, 65536);
         k_gather_f64<<<(unsigned)b, 256, 0, ctx->stream>>>(ctx->n_obs, ctx->s_from_t, ctx->t_sig_eff,
