@@ -267,16 +267,19 @@ struct AcRecord {
 // An interval of 15 to 300 observations by itself leaves 29% to 88% of the
 // lanes' slots filled and starts the loads anew each time; over eight they
 // follow on (97%; 4 and 16 intervals: 4% and 2% slower at 1.6 million intervals).
-// Fewer intervals with more records each are shared out more evenly in
-// shorter ranges: agis_ac_pass_range below.  A SIMD's
-// FP64 products and FP64 arithmetic share a pipe within a wavefront but not
-// between them, and no unit is busy for more than half of the time: latencies
-// bound it, at three wavefronts per SIMD (168 registers and 12 bytes of scratch a
-// lane, robust 100; 12.4 KB).  1M sources, 223M observations: 7.65 -> 5.17 ms (27
-// bytes of columns and, by source, a seventh of a 64-byte record per
-// observation; variants, against 5.29 before the shorter rows: two wavefronts
-// 5.9; the next columns asked for before the rows are written 5.37; 12 of 16
-// blocks by v_mfma_f64_4x4x4, whose operands take two more reads, 5.49).
+// Fewer intervals with more records each are shared out more evenly in shorter
+// ranges: agis_ac_pass_range below.
+//
+// A SIMD's FP64 products and FP64 arithmetic share a pipe within a wavefront but
+// not between them.  Counters at 223M observations: vector issue 57% of the
+// SIMDs' cycles, matrix unit 32%, no bank conflicts, 2.9 wavefronts per SIMD
+// that wait for 47% of their time: latencies bound it, at three wavefronts per
+// SIMD (168 registers and 12 bytes of scratch a lane, robust 100; 12.4 KB).  1M
+// sources, 223M observations: 7.65 -> 5.17 ms (27 bytes of columns and, by
+// source, a seventh of a 64-byte record per observation; variants, against 5.29
+// before the shorter rows: two wavefronts 5.9; the next columns asked for before
+// the rows are written 5.37; 12 of 16 blocks by v_mfma_f64_4x4x4, whose operands
+// take two more reads, 5.49).
 //
 // Mixed precision (MIXED): the model stays FP64; a and b are formed in FP32
 // from single-precision partials, each 64-observation chunk is summed by

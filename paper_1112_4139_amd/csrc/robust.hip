@@ -403,7 +403,8 @@ __global__ __launch_bounds__(256, 2) void k_s_rows(DevConsts k, int64_t n_src, c
                                                    const double* __restrict__ knots,
                                                    const KnotTab* __restrict__ ktab, const double* __restrict__ a,
                                                    const double* __restrict__ c, const double* __restrict__ s,
-                                                   const double* __restrict__ eps_a2, double* __restrict__ col, int64_t n_obs,
+                                                   const double* __restrict__ eps_a2, double* __restrict__ col,
+                                                   int64_t n_obs,
                                                    const int32_t* __restrict__ order) {
     constexpr int GPB = 256 / G;
     const int gl = threadIdx.x % G;
@@ -1076,7 +1077,8 @@ __global__ __launch_bounds__(NT) void k_s_robust(DevConsts k, int64_t n_src, int
                                                  const int32_t* __restrict__ ocell, const int32_t* __restrict__ oell,
                                                  const double* __restrict__ knots, const KnotTab* __restrict__ ktab,
                                                  const double* __restrict__ a, const double* __restrict__ c,
-                                                 const double* __restrict__ eps_a2, double* __restrict__ s, SrcPrep* __restrict__ prep,
+                                                 const double* __restrict__ eps_a2, double* __restrict__ s,
+                                                 SrcPrep* __restrict__ prep,
                                                  double* __restrict__ ds, double* __restrict__ qsrc,
                                                  int32_t* __restrict__ sdef, double* __restrict__ svar,
                                                  const int32_t* __restrict__ order, double* __restrict__ vs_out,
