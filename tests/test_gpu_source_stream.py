@@ -1,9 +1,8 @@
-"""The source update's record stream at its edges: 8 to 64 lanes per source,
-wavefronts whose 64 records lie in a few knot intervals (nine-record transits)
-and in up to 64 (single-record ones, more than the loads ahead hold), sources
-without observations and fewer sources than a block takes, across-scan records,
-and unequally spaced knots, whose attitude also puts the field angles beyond
-the range of their series.
+"""The source update at its edges: 8 to 64 lanes per source, nine-record
+transits and single-record ones, sources without observations and fewer sources
+than a block takes (whose sums its first wavefront finishes), across-scan
+records, and unequally spaced knots, whose attitude also puts the field angles
+beyond the range of their series.
 
 An update may differ from the extended-precision oracle's by 1e-3 uas, the
 parity target of every update, or by ten times the double-precision oracle's
